@@ -340,165 +340,123 @@ __device__ inline void gather_corner(const GridView& g, const Cell& c, float v[8
 }
 
 // Wave-cooperative gather of the 64 lanes' corner records (all 64 lanes of
-// the wave must call it together).  The 64 records x 6 sixteen-byte chunks
-// are spread over the lanes in two halves of 32 records, so one load
-// instruction touches about 11 records (cache lines and address translations)
-// instead of 64 and each line is read by 6 neighbouring lanes.  The six loads
-// of a lane go straight from memory into `stage` (a 64 x 24-float LDS area
-// private to the wave; 16-byte global-to-LDS loads, which place lane l's chunk
-// at byte 16 l of the instruction's destination), all in flight together and
-// holding no registers; then every lane reads its own record back.
-constexpr int COOP_STAGE_FLOAT4 = 384;   // float4 slots of one wave's staging area
+// the wave must call it together) into `stage`, an LDS area private to the wave
+// that keeps one record per lane, by 16-byte global-to-LDS loads (lane l's
+// chunk lands at byte 16 l of the instruction's destination), all in flight
+// together and holding no registers.  What bounds it: with the chip full, the
+// rate of record requests (about 4.7e10 per second for a 512^3 FP32 grid); with
+// fewer candidates, the latency of one gather, and the instructions around it.
+//
+// A record is moved by 64-byte pieces (FP32: 2, the second half pad; FP64:
+// 3), each by four neighbouring lanes: lane l fetches for record 16 k + l / 4,
+// so one record number is shuffled across per 16 records, and the pieces of a
+// record follow each other with the same address registers.  Issuing a
+// record's pieces several instructions apart touches its line again while it
+// is under way: 18% slower on 1e6 candidates in a 512^3 FP32 grid (214 against
+// 180 ms).  The earlier mapping (chunk i of the wave's 384 or 768 chunks by lane
+// i mod 64) took a shuffle, an address and a mask test per chunk: 107 against
+// 95 ms on 1e5 candidates in a 256^3 FP64 grid, where few records of a wave
+// miss, and 181 against 180 ms in the 512^3 FP32 grid.  Within a piece the
+// chunks are XOR-swizzled by the record number, so that the read-back of 16
+// consecutive lanes covers all LDS banks (it had 4-way conflicts for FP64).
+template <class GT>
+constexpr int coop_pieces = sizeof(GT) == 8 ? 3 : 2;      // 64-byte pieces per record
+template <class GT>
+constexpr int coop_stage_float4 = 256 * coop_pieces<GT>;  // 16-byte slots of a wave's area
+template <class GT>
+constexpr uint32_t record_bytes = 64u * coop_pieces<GT>;
 
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 
+// Sentinel of a lane whose record is not fetched (no grid has that many cells).
+constexpr uint32_t NO_RECORD = 0xffffffffu;
+
+// One 16-byte global-to-LDS load per active lane, from src + OFF to dst: the
+// instruction's offset applies to both addresses.
+template <int OFF>
+__device__ inline void coop_load(const char* src, char* dst)
+{
+    __builtin_amdgcn_global_load_lds((const void*)src, (lds_void_ptr)(dst - OFF), 16, OFF, 0);
+}
+
+// Byte of a piece that this lane fetches (its chunk, swizzled).
+__device__ inline int coop_byte(int lane) { return 16 * ((lane & 3) ^ ((lane >> 4) & 3)); }
+
+// The loads of a record's pieces into the slots of record group k.
+template <class GT>
+__device__ inline void coop_load_record(const char* r, char* st, int k)
+{
+    coop_load<0>(r, st + 1024 * k);
+    coop_load<64>(r, st + 4096 + 1024 * k);
+    if constexpr (sizeof(GT) == 8)
+        coop_load<128>(r, st + 8192 + 1024 * k);
+}
+
 // Issue half: the loads of the records of lanes with `need` into the staging
-// area (records no lane needs are not fetched).
-__device__ inline void coop_issue(const float* corner, uint32_t cell, float* stage, bool need)
+// area (the other lanes' slots keep what they hold).
+template <class GT>
+__device__ inline void coop_issue(const GT* corner, uint32_t cell, float* stage, bool need)
 {
     const int lane = (int)(threadIdx.x & 63u);
-    float4* st = (float4*)stage;
-    const uint64_t needm = __ballot(need);
+    char* st = (char*)stage;
+    const int mine = need ? (int)cell : (int)NO_RECORD;
+    const char* src = (const char*)corner + coop_byte(lane);
+    uint32_t rc[4];
 #pragma unroll
-    for (int half = 0; half < 2; ++half)
+    for (int k = 0; k < 4; ++k)
+        rc[k] = (uint32_t)__shfl(mine, 16 * k + (lane >> 2));
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const int idx = 64 * j + lane;            // 0..191
-            const int r = idx / 6, c = idx - 6 * r;   // record within the half, chunk
-            const int owner = 32 * half + r;
-            const uint32_t rc = (uint32_t)__shfl((int)cell, owner);
-            const float4* src = (const float4*)(corner + (uint64_t)rc * 32u) + c;
-            if ((needm >> owner) & 1ull)
-                __builtin_amdgcn_global_load_lds((const void*)src,
-                                                 (lds_void_ptr)(st + 192 * half + 64 * j), 16, 0,
-                                                 0);
-        }
+    for (int k = 0; k < 4; ++k)
+        if (rc[k] != NO_RECORD)
+            coop_load_record<GT>(src + (uint64_t)rc[k] * record_bytes<GT>, st, k);
 }
 
-// Consume half: waits for the loads, then every lane reads its own record
-// (lanes whose record was not fetched get whatever the area holds).
-__device__ inline void coop_consume(const float* stage, float v[8][3])
-{
-    const int lane = (int)(threadIdx.x & 63u);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    float f[24];
-    const float4* my = (const float4*)stage + 192 * (lane >> 5) + 6 * (lane & 31);
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-        const float4 x = my[q];
-        f[4 * q + 0] = x.x;
-        f[4 * q + 1] = x.y;
-        f[4 * q + 2] = x.z;
-        f[4 * q + 3] = x.w;
-    }
-    // the staging area is rewritten by the wave's next gather
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        v[k][0] = f[3 * k + 0];
-        v[k][1] = f[3 * k + 1];
-        v[k][2] = f[3 * k + 2];
-    }
-}
-
-// As coop_issue, for records given by a per-lane address (records of several
-// arrays, e.g. the levels of a multi-resolution grid).
+// As coop_issue, for FP32 records given by a per-lane address (records of
+// several arrays, e.g. the levels of a multi-resolution grid).
 __device__ inline void coop_issue_rec(const float* rec, float* stage, bool need)
 {
     const int lane = (int)(threadIdx.x & 63u);
-    float4* st = (float4*)stage;
-    const uint64_t needm = __ballot(need);
-    const uint64_t a = (uint64_t)(uintptr_t)rec;
+    char* st = (char*)stage;
+    const uint64_t a = need ? (uint64_t)(uintptr_t)rec : 0ull;
     const int lo = (int)(uint32_t)a, hi = (int)(uint32_t)(a >> 32);
+    uint64_t ra[4];
 #pragma unroll
-    for (int half = 0; half < 2; ++half)
+    for (int k = 0; k < 4; ++k)
+        ra[k] = ((uint64_t)(uint32_t)__shfl(hi, 16 * k + (lane >> 2)) << 32) |
+                (uint64_t)(uint32_t)__shfl(lo, 16 * k + (lane >> 2));
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-            const int idx = 64 * j + lane;            // 0..191
-            const int r = idx / 6, c = idx - 6 * r;   // record within the half, chunk
-            const int owner = 32 * half + r;
-            const uint64_t ra = ((uint64_t)(uint32_t)__shfl(hi, owner) << 32) |
-                                (uint64_t)(uint32_t)__shfl(lo, owner);
-            const float4* src = (const float4*)(uintptr_t)ra + c;
-            if ((needm >> owner) & 1ull)
-                __builtin_amdgcn_global_load_lds((const void*)src,
-                                                 (lds_void_ptr)(st + 192 * half + 64 * j), 16, 0,
-                                                 0);
-        }
+    for (int k = 0; k < 4; ++k)
+        if (ra[k] != 0ull)
+            coop_load_record<float>((const char*)(uintptr_t)ra[k] + coop_byte(lane), st, k);
 }
 
-__device__ inline void gather_corner_coop(const float* corner, uint32_t cell, float* stage,
-                                          float v[8][3], bool need)
-{
-    coop_issue(corner, cell, stage, need);
-    coop_consume(stage, v);
-}
-
-// FP64 corner records: the 8 corner vectors as 24 doubles, 192 bytes with no
-// pad, so that every record spans exactly two 128-byte lines.  The wave's 64
-// records x 12 sixteen-byte chunks take twelve loads, chunk c of record r
-// landing in float4 slot 12 r + c of the staging area (12 KiB per wave).
-constexpr int COOP_STAGE64_FLOAT4 = 768;
-
+// Consume half: waits for the loads, then every lane reads its own record
+// (lanes whose record was never fetched get whatever the area holds).
 template <class GT>
-constexpr int coop_stage_float4 = sizeof(GT) == 8 ? COOP_STAGE64_FLOAT4 : COOP_STAGE_FLOAT4;
-
-__device__ inline void coop_issue(const double* corner, uint32_t cell, float* stage, bool need)
+__device__ inline void coop_consume(const float* stage, GT v[8][3])
 {
-    const int lane = (int)(threadIdx.x & 63u);
-    float4* st = (float4*)stage;
-    const uint64_t needm = __ballot(need);
-    // partly rolled: the fully unrolled form keeps all twelve addresses live
-    // and made the FP64 method spill (30% slower on the 256^3 workload)
-#pragma unroll 4
-    for (int j = 0; j < 12; ++j) {
-        const int idx = 64 * j + lane;            // 0..767
-        const int r = idx / 12, c = idx - 12 * r;  // record (= owning lane), chunk
-        const uint32_t rc = (uint32_t)__shfl((int)cell, r);
-        const float4* src = (const float4*)(corner + (uint64_t)rc * 24u) + c;
-        if ((needm >> r) & 1ull)
-            __builtin_amdgcn_global_load_lds((const void*)src, (lds_void_ptr)(st + 64 * j), 16,
-                                             0, 0);
-    }
-}
-
-__device__ inline void coop_consume(const float* stage, double v[8][3])
-{
+    constexpr int NC = sizeof(GT) == 8 ? 12 : 6;   // chunks of values
     const int lane = (int)(threadIdx.x & 63u);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    double f[24];
-    const double2* my = (const double2*)stage + 12 * lane;
+    const char* q4 = (const char*)stage + 64 * lane;
+    const int s4 = 16 * ((lane >> 2) & 3);
+    constexpr int EPC = 16 / (int)sizeof(GT);   // elements per chunk
 #pragma unroll
-    for (int q = 0; q < 12; ++q) {
-        const double2 x = my[q];
-        f[2 * q + 0] = x.x;
-        f[2 * q + 1] = x.y;
+    for (int q = 0; q < NC; ++q) {
+        GT e[EPC];
+        __builtin_memcpy(e, __builtin_assume_aligned(q4 + (s4 ^ (16 * (q & 3))) + 4096 * (q >> 2), 16),
+                         16);
+#pragma unroll
+        for (int i = 0; i < EPC; ++i)
+            v[(EPC * q + i) / 3][(EPC * q + i) % 3] = e[i];
     }
     // the staging area is rewritten by the wave's next gather
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        v[k][0] = f[3 * k + 0];
-        v[k][1] = f[3 * k + 1];
-        v[k][2] = f[3 * k + 2];
-    }
-}
-
-__device__ inline void gather_corner_coop(const double* corner, uint32_t cell, float* stage,
-                                          double v[8][3], bool need)
-{
-    coop_issue(corner, cell, stage, need);
-    coop_consume(stage, v);
 }
 
 // The corner records of a grid's element type.
@@ -559,13 +517,14 @@ __device__ inline void interp_fp32(const double t[3], const GT v[8][3], float B[
 template <class GT, int LAYOUT>
 struct GridField {
     GridView g;
-    float* stage = nullptr;   // LAYOUT 2: the wave's LDS staging area
-    // need = false: this lane's value will not be used (the cooperative
-    // gather then skips its record; the per-lane gathers skip the loads)
-    __device__ inline void corners(const Cell& c, GT v[8][3], bool need) const
+    float* stage = nullptr;        // LAYOUT 2: the wave's LDS staging area
+    uint32_t have = NO_RECORD;     // LAYOUT 2: the record this lane's slot holds
+    // need = false: this lane's value will not be used (its loads are skipped)
+    __device__ inline void corners(const Cell& c, GT v[8][3], bool need)
     {
         if constexpr (LAYOUT == 2) {
-            gather_corner_coop(corner_records<GT>(g), (uint32_t)cell_index(g, c), stage, v, need);
+            fetch(c, need);
+            coop_consume(stage, v);
         } else if (need) {
             if constexpr (LAYOUT == 1)
                 gather_corner(g, c, v);
@@ -577,14 +536,31 @@ struct GridField {
                 v[k][0] = v[k][1] = v[k][2] = (GT)0;
         }
     }
-    __device__ inline void fp64(const double p[3], double B[3], bool need = true) const
+    // LAYOUT 2: issues the loads of the lanes' records, except those that the
+    // staging area already holds: consecutive stages of an attempt, and the
+    // position it moves to, often fall in one cell.  Counted on the CPU, requests
+    // per attempt fall from 5.77 to 5.27 on 10 kpc cells (mean step ~15 cells)
+    // and from 5.51 to 2.20 on 50 kpc cells with a field of 2..16 cells; with the
+    // first stage's record fetched for new candidates too (no empty sixth
+    // gather), 1e5 candidates in a 256^3 FP64 grid took 144 -> 95 ms, 1e6 in a
+    // 512^3 FP32 grid 189 -> 180 ms.
+    __device__ inline void fetch(const Cell& c, bool need)
+    {
+        const uint32_t cell = (uint32_t)cell_index(g, c);
+        const bool miss = need && cell != have;
+        if (__ballot(miss) != 0ull) {
+            coop_issue(corner_records<GT>(g), cell, stage, miss);
+            have = miss ? cell : have;
+        }
+    }
+    __device__ inline void fp64(const double p[3], double B[3], bool need = true)
     {
         const Cell c = locate(g, p);
         GT v[8][3];
         corners(c, v, need);
         interp_fp64(c.t, v, B);
     }
-    __device__ inline void fp32(const double p[3], float B[3], bool need = true) const
+    __device__ inline void fp32(const double p[3], float B[3], bool need = true)
     {
         const Cell c = locate(g, p);
         GT v[8][3];
@@ -600,12 +576,11 @@ struct GridField {
 
     // Split evaluation (cooperative layout only): prefetch() issues the loads
     // of B(p) for the lanes with `need`; a later *_prefetched(p) with the same
-    // p completes it.  Nothing else may use the staging area in between.
-    __device__ inline void prefetch(const double p[3], bool need) const
+    // p completes it.  In between only other lanes may be prefetched.
+    __device__ inline void prefetch(const double p[3], bool need)
     {
         static_assert(LAYOUT == 2, "split evaluation needs the cooperative layout");
-        const Cell c = locate(g, p);
-        coop_issue(corner_records<GT>(g), (uint32_t)cell_index(g, c), stage, need);
+        fetch(locate(g, p), need);
     }
     __device__ inline void fp32_prefetched(const double p[3], float B[3]) const
     {
@@ -648,6 +623,7 @@ struct NestedField {
     const PatchView* P = nullptr;
     int np = 0;
     float* stage = nullptr;   // COOP: the wave's LDS staging area
+    const float* have = nullptr;   // COOP: the record this lane's slot holds
     // the first patch's parameters, kept in (scalar) registers for the common
     // single-patch case, so that its test reads no LDS
     const float* c0 = nullptr;
@@ -764,12 +740,21 @@ struct NestedField {
             }
         }
     }
-    __device__ inline void fp64(const double p[3], double B[3], bool need = true) const
+    // COOP: as GridField::fetch
+    __device__ inline void fetch(const float* rec, bool need)
+    {
+        const bool miss = need && rec != have;
+        if (__ballot(miss) != 0ull) {
+            coop_issue_rec(rec, stage, miss);
+            have = miss ? rec : have;
+        }
+    }
+    __device__ inline void fp64(const double p[3], double B[3], bool need = true)
     {
         double t[3];
         if constexpr (COOP) {
             float v[8][3];
-            coop_issue_rec(record(p, t), stage, need);
+            fetch(record(p, t), need);
             coop_consume(stage, v);
             interp_fp64(t, v, B);
         } else {
@@ -778,12 +763,12 @@ struct NestedField {
             interp_fp64(t, v, B);
         }
     }
-    __device__ inline void fp32(const double p[3], float B[3], bool need = true) const
+    __device__ inline void fp32(const double p[3], float B[3], bool need = true)
     {
         double t[3];
         if constexpr (COOP) {
             float v[8][3];
-            coop_issue_rec(record(p, t), stage, need);
+            fetch(record(p, t), need);
             coop_consume(stage, v);
             interp_fp32(t, v, B);
         } else {
@@ -800,11 +785,11 @@ struct NestedField {
     }
     // Split evaluation (COOP only), as GridField's: prefetch() issues the
     // record loads of B(p); *_prefetched(p) with the same p completes it.
-    __device__ inline void prefetch(const double p[3], bool need) const
+    __device__ inline void prefetch(const double p[3], bool need)
     {
         static_assert(COOP, "split evaluation needs the cooperative gather");
         double t[3];
-        coop_issue_rec(record(p, t), stage, need);
+        fetch(record(p, t), need);
     }
     __device__ inline void fp32_prefetched(const double p[3], float B[3]) const
     {
@@ -898,26 +883,14 @@ __device__ inline void deriv_from_field(double kappa, const double y[6], const d
     k[5] = kappa * c[2];
 }
 
-// `need`: this lane's result is used.  `reuse`: b1 already holds B(x) of this
-// very position (a retry after a rejected attempt), so the first stage does
-// not gather it again; otherwise b1 receives B(x).
+// `need`: this lane's result is used.  b1: the field at x (kept over the
+// retries of a rejected attempt, which start from the same position).
 template <class F>
-__device__ inline double ck_attempt_fp64(const F& field, double kappa, const double y[6],
-                                         double h, double y5[6], bool need, bool reuse,
-                                         double b1[3])
+__device__ inline double ck_attempt_fp64(F& field, double kappa, const double y[6], double h,
+                                         double y5[6], bool need, const double b1[3])
 {
     double K[6][6];
-    {
-        double B[3];
-        field.fp64(y, B, need && !reuse);
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            if (reuse)
-                B[q] = b1[q];
-            b1[q] = B[q];
-        }
-        deriv_from_field(kappa, y, B, K[0]);
-    }
+    deriv_from_field(kappa, y, b1, K[0]);
 #pragma unroll
     for (int i = 1; i < 6; ++i) {
         double ys[6];
@@ -970,26 +943,16 @@ __device__ inline void incr_from_field(float hf, float hk, const float u[3], con
     G[5] = hk * c[2];
 }
 
-// need / reuse / b1 as for ck_attempt_fp64 (b1 in FP32).
+// need / b1 as for ck_attempt_fp64 (b1 in FP32).
 template <class F>
-__device__ inline double ck_attempt_mix_f(const F& field, double kappa, const double x[3],
+__device__ inline double ck_attempt_mix_f(F& field, double kappa, const double x[3],
                                           const float u[3], double h, double x5[3],
-                                          float u5[3], bool need, bool reuse, float b1[3])
+                                          float u5[3], bool need, const float b1[3])
 {
     const float hf = (float)h;
     const float hk = (float)(h * kappa);
     float G[6][6];
-    {
-        float B[3];
-        field.fp32(x, B, need && !reuse);
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            if (reuse)
-                B[q] = b1[q];
-            b1[q] = B[q];
-        }
-        incr_from_field(hf, hk, u, B, G[0]);
-    }
+    incr_from_field(hf, hk, u, b1, G[0]);
 #pragma unroll
     for (int i = 1; i < 6; ++i) {
         float s[6];
@@ -1042,7 +1005,7 @@ __device__ inline double ck_attempt_mix_f(const F& field, double kappa, const do
 // fit the instruction cache).  The stage sums keep the index order of the
 // unrolled form: a term j >= i is skipped, not added as zero.
 template <class F>
-__device__ inline double ck_attempt_mix_rolled(const F& field, double kappa, const double x[3],
+__device__ inline double ck_attempt_mix_rolled(F& field, double kappa, const double x[3],
                                                const float u[3], double h, double x5[3],
                                                float u5[3])
 {

@@ -294,6 +294,8 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
     T.lg0 = PP->tab.lg0;
     T.scale = PP->tab.scale;
 
+    // the wave's index in the block, in a scalar register
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     typename FieldOf<GT, LAYOUT>::T F;
     if constexpr (LAYOUT == 3) {
         // the network image follows the tables in dynamic LDS
@@ -309,10 +311,10 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
         F.np = PP->nest.np;
         F.set_first(PP->nest.p[0]);
         if constexpr (LAYOUT == 6)
-            F.stage = (float*)(stage_mem + (t >> 6) * COOP_STAGE_FLOAT4);
+            F.stage = (float*)(stage_mem + wave * coop_stage_float4<float>);
     } else {
         F.g = PP->grid;
-        F.stage = (float*)(stage_mem + (LAYOUT == 2 ? (t >> 6) * coop_stage_float4<GT> : 0));
+        F.stage = (float*)(stage_mem + (LAYOUT == 2 ? wave * coop_stage_float4<GT> : 0));
     }
     const StepParams sp = PP->sp;
     const int lane = lane_id();
@@ -331,13 +333,14 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
     // the lane holds a candidate whose last cycle stopped just before an
     // interaction for want of an output slot: it finishes that cycle first
     bool resume = false;
-    // field at the current position, kept for the retry after a rejection
+    // field at the current position (first stage of the next attempt, kept for
+    // the retry after a rejection).  Cooperative layouts: its record is fetched
+    // as soon as the position is known (after the attempt that moved there, or
+    // at the claim), while the rest of the cycle runs
     using BT = typename DirType<MODE>::T;
     BT b1[3] = {0, 0, 0};
-    bool reuse = false;
-    // cooperative layout: the field at the position an accepted attempt moved
-    // to is fetched while the rest of its cycle runs, for the next attempt
-    bool pref = false;
+    enum { B_NONE = 0, B_FETCHED = 1, B_KNOWN = 2 };
+    int bst = B_NONE;
     bool initial_left = true;
     // this wave's reservation of appended slots [rb, re): taken with one
     // atomicAdd, handed to idle lanes as their producers publish them
@@ -411,8 +414,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                     q.ready[slot] = 0u;   // clean for the next run
                 active = true;
                 fresh = !resume;
-                reuse = false;
-                pref = false;
+                bst = B_NONE;
             }
         }
         if (__ballot(active) == 0ull) {
@@ -444,6 +446,15 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
             continue;
         }
         backoff = 0;
+
+        // cooperative layouts: newly claimed and resumed candidates' records
+        if constexpr (wave_gather<LAYOUT>) {
+            const bool fetch = active && !resume && bst == B_NONE;
+            if (__ballot(fetch) != 0ull) {
+                F.prefetch(x, fetch);
+                bst = fetch ? B_FETCHED : bst;
+            }
+        }
 
         // ---- start of a cycle: rates and step proposal -----------------------
         if (active && fresh) {
@@ -487,21 +498,28 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
             fresh = false;
         }
 
-        // ---- the first-stage field of this position may already be on its way
+        // ---- the field at this position, where it is not yet known ----------
         if constexpr (wave_gather<LAYOUT>) {
-            if (__ballot(pref) != 0ull) {
+            if (__ballot(bst == B_FETCHED) != 0ull) {
                 BT bp[3];
                 if constexpr (MODE == MODE_FP64)
                     F.fp64_prefetched(x, bp);
                 else
                     F.fp32_prefetched(x, bp);
-                if (pref) {
+                if (bst == B_FETCHED) {
 #pragma unroll
                     for (int q = 0; q < 3; ++q)
                         b1[q] = bp[q];
-                    reuse = true;
+                    bst = B_KNOWN;
                 }
-                pref = false;
+            }
+        } else if constexpr (LAYOUT != 3) {
+            if (active && !resume && bst == B_NONE) {
+                if constexpr (MODE == MODE_FP64)
+                    F.fp64(x, b1);
+                else
+                    F.fp32(x, b1);
+                bst = B_KNOWN;
             }
         }
 
@@ -522,7 +540,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
             if constexpr (MODE == MODE_FP64) {
                 const double y[6] = {x[0], x[1], x[2], u[0], u[1], u[2]};
                 double y5[6];
-                err = ck_attempt_fp64(F, kappa, y, h, y5, stepping, reuse, b1);
+                err = ck_attempt_fp64(F, kappa, y, h, y5, stepping, b1);
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
                     x5[q] = y5[q];
@@ -532,7 +550,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                 if constexpr (LAYOUT == 3)
                     err = ck_attempt_mix_rolled(F, kappa, x, u, h, x5, u5);
                 else
-                    err = ck_attempt_mix_f(F, kappa, x, u, h, x5, u5, stepping, reuse, b1);
+                    err = ck_attempt_mix_f(F, kappa, x, u, h, x5, u5, stepping, b1);
             }
         }
         if constexpr (wave_gather<LAYOUT>) {
@@ -541,7 +559,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
             const bool acc = stepping && (err / sp.tol <= 1.0 || h <= sp.hmin);
             if (__ballot(acc) != 0ull)
                 F.prefetch(x5, acc);
-            pref = acc;
+            bst = acc ? B_FETCHED : bst;
         }
         // the cycle's energy and optical depth after the step, and whether an
         // interaction is due
@@ -552,7 +570,8 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
             const double r = err / sp.tol;
             if (r <= 1.0 || h <= sp.hmin) {
                 ev |= EV_ACCEPT;
-                reuse = false;
+                if constexpr (!wave_gather<LAYOUT>)
+                    bst = B_NONE;
                 if (r > 1.0)
                     ev |= EV_FORCED;
                 double fac = 5.0;
@@ -605,8 +624,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                 evt = unpack_flag(S.azf[t]) == LIM_INTER || tau <= 0.0;
                 cycle = true;
             } else {
-                reuse = true;             // same position: b1 holds its field
-                S.nrej[t] += 1u;
+                S.nrej[t] += 1u;          // same position: b1 keeps its field
                 double fac = (double)ctrl_k(r) / 1024.0;
                 if (fac < 0.1)
                     fac = 0.1;
@@ -1002,7 +1020,7 @@ __global__ void k_eval_field(GridView g, int64_t n, const double* pos, double* B
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n)
         return;
-    const GridField<GT, LAYOUT> F{g};
+    GridField<GT, LAYOUT> F{g};
     const double p[3] = {pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]};
     if (mode == MODE_FP64) {
         double b[3];
@@ -1097,16 +1115,18 @@ __device__ inline uint32_t mix32(uint32_t x)
 __global__ void __launch_bounds__(128) k_gather_ceiling(const float* corner, uint32_t ncell,
                                                         int iters, float* sink)
 {
-    __shared__ float4 stage[2 * COOP_STAGE_FLOAT4];
+    __shared__ float4 stage[2 * coop_stage_float4<float>];
     const int t = (int)threadIdx.x;
-    float* st = (float*)(stage + (t >> 6) * COOP_STAGE_FLOAT4);
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    float* st = (float*)(stage + wave * coop_stage_float4<float>);
     uint32_t s = mix32((uint32_t)blockIdx.x * 128u + (uint32_t)t + 0x9e3779b9u);
     float acc = 0.0f;
     for (int it = 0; it < iters; ++it) {
         s = mix32(s + 0x9e3779b9u);
         const uint32_t cell = (uint32_t)(((uint64_t)s * ncell) >> 32);   // < ncell
         float v[8][3];
-        gather_corner_coop(corner, cell, st, v, true);
+        coop_issue(corner, cell, st, true);
+        coop_consume(st, v);
         acc += v[t & 7][0];
     }
     sink[(int64_t)blockIdx.x * 128 + t] = acc;

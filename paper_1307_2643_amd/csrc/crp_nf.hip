@@ -132,7 +132,7 @@ __device__ __forceinline__ void nf_sample_xhat(const NFGeom& G, uint64_t seed, u
 __device__ __forceinline__ void nf_sample_target(const GridView& g, const NFGeom& G,
                                                  const double p[3], float tgt[3])
 {
-    const GridField<float, 0> F{g};
+    GridField<float, 0> F{g};
     float B[3];
     F.fp32(p, B);
     const float inv = 1.0f / G.b_scale;
