@@ -79,13 +79,40 @@ __device__ inline double optical_depth(uint64_t w)
     return q < 0x1p-24 ? 0x1p-24 : q;
 }
 
+// The two values taken from draw number m of candidate (id, lineage): the word
+// of the channel choice and the next optical depth.
+struct EventDraw {
+    uint64_t w0;
+    double tau;
+};
+
+__device__ inline EventDraw draw_event_inline(uint64_t seed, uint32_t id, uint32_t lineage,
+                                              uint32_t m)
+{
+    const U64x4 w = event_draw(seed, id, lineage, m);
+    return EventDraw{w.w[0], optical_depth(w.w[1])};
+}
+
+// Out of line: interactions are rare, and inlined their constants (Philox keys,
+// the logarithm's polynomial) were kept in registers through the whole stepping
+// loop.
+__device__ __attribute__((noinline)) EventDraw draw_event(uint64_t seed, uint32_t id,
+                                                          uint32_t lineage, uint32_t m)
+{
+    return draw_event_inline(seed, id, lineage, m);
+}
+
 // Uniform [0, 1) from one word: (w >> 11) 2^-53.
 __device__ inline double unit_uniform(uint64_t w) { return (double)(w >> 11) * 0x1p-53; }
 
 // -------------------------------------------------------------------------
 // Step-size factor k / 1024 with k = floor(1024 * 0.95 * r^(-1/5)) defined
 // exactly as the largest integer with k^5 r <= (0.95 * 1024)^5 in FP64 (fixed
-// order); pow() only supplies the first guess.  k is capped at 5121.
+// order), at most 5121 and 0 where there is none (NaN, infinity).  The hardware
+// log2 and exp2 in FP32 give g = 972.8 r^(-1/5) within 0.02 for every r whose k
+// lies between the ends (relative error 3e-6 of at most 5121), so the nearest
+// integer m to g is k or k + 1 and one test decides (a search from the guess
+// tested twice or more, in loops).
 // -------------------------------------------------------------------------
 __device__ inline bool ctrl_ok(int k, double r)
 {
@@ -99,21 +126,11 @@ __device__ inline bool ctrl_ok(int k, double r)
 __device__ inline int ctrl_k(double r)
 {
     const int KMAX = 5121;
-    // first guess from the hardware log2/exp2 in FP32 (a few ulp off at most);
-    // the exact search below decides
-    int k = KMAX;
-    if (r > 1e-30) {
-        const float rf = r < 1e30 ? (float)r : 1e30f;
-        const float g = 972.8f * __builtin_amdgcn_exp2f(-0.2f * __builtin_amdgcn_logf(rf));
-        k = g >= (float)KMAX ? KMAX : (g >= 1.0f ? (int)g : 0);
-    } else if (!(r >= 0.0)) {
-        k = 0;   // NaN
-    }
-    while (k < KMAX && ctrl_ok(k + 1, r))
-        ++k;
-    while (k > 0 && !ctrl_ok(k, r))
-        --k;
-    return k;
+    const double rc = r < 1e-30 ? 1e-30 : (r < 1e30 ? r : 1e30);
+    const float g = 972.8f * __builtin_amdgcn_exp2f(-0.2f * __builtin_amdgcn_logf((float)rc));
+    const int m = min((int)(g + 0.5f), KMAX);
+    const int k = ctrl_ok(m, r) ? m : m - 1;
+    return max(k, 0);
 }
 
 // -------------------------------------------------------------------------
@@ -208,7 +225,8 @@ struct GridView {
     const float* corner;    // FP32 grid: corner records [nx][ny][nz][32] (float) or null
     const double* corner64; // FP64 grid: corner records [nx][ny][nz][24] (double) or null
     int n[3];
-    int mask[3];            // n-1 if n is a power of two, else -1
+    int pow2;               // every n is a power of two
+    double inv_n[3];        // 1 / n, rounded once
     int64_t stride[3];      // elements: ny*nz*3, nz*3, 3
     double inv_spacing;     // 1 / spacing, rounded once
     double origin[3];
@@ -237,12 +255,25 @@ struct NestView {
     PatchView p[MAX_PATCHES];
 };
 
-__device__ inline int wrap_index(int i, int n, int mask)
+// A double in int32 range as an int, truncating (the hardware conversion, whose
+// result is also defined, though not used, for the other doubles).
+__device__ inline int cvt_i32(double v)
 {
-    if (mask >= 0)
-        return i & mask;
-    int r = i % n;
-    return r < 0 ? r + n : r;
+    int r;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+
+// Periodic index of the cell offset fl (an integer, |fl| < 2^31) on an axis of n
+// cells: fl - n floor(fl / n).  The quotient fl * (1/n) is within 2^-20.4 / n of
+// fl / n, less than the distance of any non-multiple to the next integer above,
+// so its floor q is exact or, for a multiple of n, one too small; fl - q n is
+// exact (integers below 2^53) and lies in [0, n].
+__device__ inline int wrap_index(double fl, int n, double inv_n)
+{
+    const double q = floor(fl * inv_n);
+    const uint32_t i = (uint32_t)cvt_i32(__builtin_fma(-q, (double)n, fl));
+    return (int)min(i, i - (uint32_t)n);   // i - n wraps to a large value for i < n
 }
 
 // Cell of a position some 2^31 or more cells out on some axis (as a forced
@@ -275,18 +306,24 @@ __device__ inline Cell locate(const GridView& g, const double p[3])
 {
     Cell c;
     double fl[3];
-    bool near = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const double f = (p[a] - g.origin[a]) * g.inv_spacing;
         fl[a] = floor(f);
-        near = near & (fabs(fl[a]) < 0x1p31);   // false for a non-finite offset
-        // the conversion is only used for offsets within 32 bits; the clamp
-        // keeps it defined for the others, which far_cells then replaces
-        const double fc = fmin(fmax(fl[a], -0x1p31), 0x1p31 - 1.0);
-        c.i0[a] = wrap_index((int)fc, g.n[a], g.mask[a]);
         c.t[a] = f - fl[a];
     }
+    if (g.pow2) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            c.i0[a] = cvt_i32(fl[a]) & (g.n[a] - 1);
+    } else {
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            c.i0[a] = wrap_index(fl[a], g.n[a], g.inv_n[a]);
+    }
+    // offsets of 2^31 cells or more (false too for a non-finite offset); nearer
+    // ones beyond the sum's bound get the same cells from far_cells
+    const bool near = (fabs(fl[0]) + fabs(fl[1])) + fabs(fl[2]) < 0x1p31;
     if (__builtin_expect(!near, 0)) {
         const CellIdx r = far_cells(g.n[0], g.n[1], g.n[2], fl[0], fl[1], fl[2]);
 #pragma unroll

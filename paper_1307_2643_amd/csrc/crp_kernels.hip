@@ -58,27 +58,15 @@ __device__ inline void store_cand(const QueueSoA& q, int64_t i, const Cand& c)
     q.Z[i] = c.Z;
 }
 
-// Bookkeeping: block counters in LDS; the per-iteration counts (attempts,
-// accepts, forced accepts) are added once per wave from a ballot, rare events
-// with an LDS atomic where they happen.
+// Bookkeeping: block counters in LDS.  Each lane counts its candidate's steps,
+// rejected attempts and forced steps of this run in registers (none can pass
+// 2^32 before the candidate's own 32-bit counts do) and adds them when the
+// candidate ends or is parked; rare events are added where they happen.
 enum {
     WC_STEPS = 0, WC_ATTEMPTS, WC_REJECTS, WC_FORCED, WC_EVENTS, WC_NULL, WC_PI, WC_N,
     WC_FINISHED, WC_OBSERVED, WC_MAXTRAJ, WC_EFLOOR, WC_QDEFER, WC_NDEFER, WC_LANES, WC_BOUNDARY,
     WC_COUNT
 };
-enum : uint32_t { EV_ATTEMPT = 1u << 0, EV_ACCEPT = 1u << 1, EV_FORCED = 1u << 2, EV_FIN = 1u << 3 };
-
-__device__ inline unsigned long long count_bit(uint32_t ev, uint32_t bit)
-{
-    return (unsigned long long)__popcll(__ballot((ev & bit) != 0u));
-}
-
-// Adds a wave-uniform count to the block's LDS counter.
-__device__ inline void add_count(unsigned long long* bc, int i, unsigned long long v)
-{
-    if (v != 0ull && lane_id() == 0)
-        atomicAdd(bc + i, v);
-}
 
 // Destination of each block counter in the device counter block.
 __device__ inline unsigned long long* count_dst(DevCounters* cnt, int i)
@@ -166,17 +154,24 @@ constexpr uint32_t IDLE_SLEEP_LIMIT = 1u << 23;
 // position, direction, step and curvature occupy registers in the attempt.
 template <int BS>
 struct LaneShared {
-    double E[BS], L[BS], Lmax[BS], hctrl[BS], tau[BS], R[BS], beta[BS];
-    uint32_t id[BS], lineage[BS], m[BS], nsteps[BS], nrej[BS], cycles[BS];
-    uint32_t azf[BS];   // A | Z << 8 | step-limit flag << 16
+    double E[BS], L[BS], Lmax[BS], tau[BS], R[BS], beta[BS];
+    uint32_t id[BS], lineage[BS], m[BS];
+    uint32_t nsteps[BS], nrej[BS];   // as claimed (without this run's counts)
+    uint32_t azf[BS];   // A | Z << 8 | step-limit flag << 16 | claimed to resume << 24
 };
 
 __device__ inline int unpack_A(uint32_t v) { return (int)(v & 0xffu); }
 __device__ inline int unpack_Z(uint32_t v) { return (int)((v >> 8) & 0xffu); }
 __device__ inline int unpack_flag(uint32_t v) { return (int)((v >> 16) & 0xffu); }
-__device__ inline uint32_t pack_azf(int A, int Z, int flag)
+__device__ inline int unpack_resumed(uint32_t v) { return (int)(v >> 24); }
+__device__ inline uint32_t pack_azf(int A, int Z, int flag, int resumed)
 {
-    return (uint32_t)A | ((uint32_t)Z << 8) | ((uint32_t)flag << 16);
+    return (uint32_t)A | ((uint32_t)Z << 8) | ((uint32_t)flag << 16) | ((uint32_t)resumed << 24);
+}
+// The same with another step-limit flag.
+__device__ inline uint32_t with_flag(uint32_t v, int flag)
+{
+    return (v & 0xff00ffffu) | ((uint32_t)flag << 16);
 }
 
 // Hides a pointer's value from the optimiser so that loads through it stay
@@ -218,6 +213,22 @@ struct FieldOf<GT, 6> {
 // Layouts whose field values are gathered by the whole wave together.
 template <int LAYOUT>
 constexpr bool wave_gather = LAYOUT == 2 || LAYOUT == 6;
+
+// An event's draws: out of line except in the neural stepper, whose network
+// evaluation takes accumulation registers that a kernel with calls gives up
+// (54 against 42 ms on 6e4 candidates).
+template <int LAYOUT>
+__device__ inline EventDraw draw(uint64_t seed, uint32_t id, uint32_t lineage, uint32_t m)
+{
+    if constexpr (LAYOUT == 3)
+        return draw_event_inline(seed, id, lineage, m);
+    else
+        return draw_event(seed, id, lineage, m);
+}
+
+// 16-byte slots of a wave's LDS staging area.
+template <class GT, int LAYOUT>
+constexpr int stage_float4 = wave_gather<LAYOUT> ? coop_stage_float4<GT> : 0;
 
 template <int MODE>
 struct DirType {
@@ -263,8 +274,8 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
     extern __shared__ __attribute__((aligned(16))) double lds[];
     __shared__ LaneShared<BS> S;              // per-lane cold state
     __shared__ unsigned long long bc[WC_COUNT];   // block bookkeeping counters
-    // LDS staging of the wave-cooperative corner gather (LAYOUT 2 and 6 only)
-    __shared__ float4 stage_mem[wave_gather<LAYOUT> ? BS / 64 * coop_stage_float4<GT> : 1];
+    // the waves' staging areas: the lanes' corner records
+    __shared__ float4 stage_mem[stage_float4<GT, LAYOUT> > 0 ? BS / 64 * stage_float4<GT, LAYOUT> : 1];
     // patch table of the multi-resolution grid (LAYOUT 5 only)
     __shared__ PatchView nest_lds[LAYOUT == 5 || LAYOUT == 6 ? MAX_PATCHES : 1];
     const int t = (int)threadIdx.x;
@@ -311,10 +322,10 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
         F.np = PP->nest.np;
         F.set_first(PP->nest.p[0]);
         if constexpr (LAYOUT == 6)
-            F.stage = (float*)(stage_mem + wave * coop_stage_float4<float>);
+            F.stage = (float*)(stage_mem + wave * stage_float4<GT, LAYOUT>);
     } else {
         F.g = PP->grid;
-        F.stage = (float*)(stage_mem + (LAYOUT == 2 ? wave * coop_stage_float4<GT> : 0));
+        F.stage = (float*)(stage_mem + wave * stage_float4<GT, LAYOUT>);
     }
     const StepParams sp = PP->sp;
     const int lane = lane_id();
@@ -330,6 +341,10 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
     double h = 0.0, kappa = 0.0;
     int64_t slot = 0;
     bool active = false, fresh = true;
+    // S.R, S.beta and kappa belong to the candidate's present species and energy
+    bool rated = false;
+    uint32_t nacc = 0u, nrejd = 0u, nforced = 0u;   // this candidate's counts in this run
+    uint64_t iters = 0;                             // attempts of the wave
     // the lane holds a candidate whose last cycle stopped just before an
     // interaction for want of an output slot: it finishes that cycle first
     bool resume = false;
@@ -398,22 +413,22 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                 S.E[t] = q.E[slot];
                 S.L[t] = q.L[slot];
                 S.Lmax[t] = q.Lmax[slot];
-                S.hctrl[t] = q.hctrl[slot];
+                h = q.hctrl[slot];
                 S.tau[t] = q.tau[slot];
                 S.id[t] = q.id[slot];
                 S.lineage[t] = q.lineage[slot];
                 S.m[t] = q.m[slot];
                 S.nsteps[t] = q.nsteps[slot];
                 S.nrej[t] = q.nrej[slot];
-                S.cycles[t] = 0u;
                 resume = S.tau[t] < 0.0;
                 // a resumed cycle keeps the step limit its step had
                 S.azf[t] = pack_azf(q.A[slot], q.Z[slot],
-                                    resume ? event_due_flag(S.tau[t]) : LIM_CTRL);
+                                    resume ? event_due_flag(S.tau[t]) : LIM_CTRL, resume ? 1 : 0);
                 if ((unsigned long long)slot >= tail0)
                     q.ready[slot] = 0u;   // clean for the next run
                 active = true;
                 fresh = !resume;
+                rated = false;
                 bst = B_NONE;
             }
         }
@@ -457,15 +472,24 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
         }
 
         // ---- start of a cycle: rates and step proposal -----------------------
-        if (active && fresh) {
+        // (rates follow from species and energy: a candidate that loses none
+        // keeps them; on backtracked events they took an eighth of the
+        // instructions)
+        if (active && fresh && !rated) {
             const uint32_t azf = S.azf[t];
             const int A = unpack_A(azf), Z = unpack_Z(azf);
             const double E = S.E[t];
             const Rates rt = species_rates(T, A, Z, E);
-            const double R = rt.r, beta = rt.beta;
+            // backtracking follows the antiparticle: charge -Z
+            kappa = ((double)(sp.charge_sign * Z) * kC) / E;
+            S.R[t] = rt.r;
+            S.beta[t] = rt.beta;
+            rated = true;
+        }
+        if (active && fresh) {
+            const double R = S.R[t], beta = S.beta[t];
             const double L = S.L[t], Lmax = S.Lmax[t], tau = S.tau[t];
-            int flag = LIM_CTRL;
-            h = S.hctrl[t];
+            int flag = LIM_CTRL;   // h: the controller's step
             if (Lmax - L < h) {
                 h = Lmax - L;
                 flag = LIM_TRAJ;
@@ -490,11 +514,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                     flag = LIM_OBS;
                 }
             }
-            // backtracking follows the antiparticle: charge -Z
-            kappa = ((double)(sp.charge_sign * Z) * kC) / E;
-            S.R[t] = R;
-            S.beta[t] = beta;
-            S.azf[t] = pack_azf(A, Z, flag);
+            S.azf[t] = with_flag(S.azf[t], flag);
             fresh = false;
         }
 
@@ -524,9 +544,8 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
         }
 
         // ---- one Cash-Karp attempt -------------------------------------------
-        uint32_t ev = 0u;
         int status = ST_ACTIVE;
-        bool park = false, rec = false;
+        bool park = false, rec = false, fin = false;
         // lanes that step in this iteration (a resumed lane only finishes its
         // interrupted cycle)
         const bool stepping = active && !resume;
@@ -553,10 +572,11 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                     err = ck_attempt_mix_f(F, kappa, x, u, h, x5, u5, stepping, b1);
             }
         }
+        const double r = err / sp.tol;
+        const bool acc = stepping && (r <= 1.0 || h <= sp.hmin);
         if constexpr (wave_gather<LAYOUT>) {
             // accepted lanes move to x5: start fetching B(x5) now, so that the
             // loads overlap the rest of the cycle
-            const bool acc = stepping && (err / sp.tol <= 1.0 || h <= sp.hmin);
             if (__ballot(acc) != 0ull)
                 F.prefetch(x5, acc);
             bst = acc ? B_FETCHED : bst;
@@ -566,26 +586,22 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
         double E = 0.0, tau = 0.0;
         bool evt = false, cycle = false;
         if (stepping) {
-            ev |= EV_ATTEMPT;
-            const double r = err / sp.tol;
-            if (r <= 1.0 || h <= sp.hmin) {
-                ev |= EV_ACCEPT;
+            // step-size factor: r = 0 (and a NaN, accepted at hmin) grow by 5
+            double fac = (double)ctrl_k(r) * 0x1p-10;
+            if (acc)
+                fac = r > 0.0 && fac < 5.0 ? fac : 5.0;
+            else if (fac < 0.1)
+                fac = 0.1;
+            double hn = h * fac;
+            if (hn < sp.hmin)
+                hn = sp.hmin;
+            if (acc) {
                 if constexpr (!wave_gather<LAYOUT>)
                     bst = B_NONE;
-                if (r > 1.0)
-                    ev |= EV_FORCED;
-                double fac = 5.0;
-                if (r > 0.0) {
-                    fac = (double)ctrl_k(r) / 1024.0;
-                    if (fac > 5.0)
-                        fac = 5.0;
-                }
-                double hn = h * fac;
-                if (hn < sp.hmin)
-                    hn = sp.hmin;
+                nacc += 1u;
+                nforced += r > 1.0 ? 1u : 0u;
                 if (hn > sp.hmax)
                     hn = sp.hmax;
-                S.hctrl[t] = hn;
                 // integration module: position, direction, trajectory length
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
@@ -609,30 +625,28 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                 }
                 const double L = S.L[t] + h;
                 S.L[t] = L;
-                S.nsteps[t] += 1u;
-                // continuous loss: (2,2) Pade form of exp(-beta h)
+                // continuous loss: (2,2) Pade form of exp(-beta h), 1 where
+                // beta is 0 (12 / 12)
                 E = S.E[t];
-                {
-                    const double z = S.beta[t] * h;
+                const double beta = S.beta[t];
+                if (beta != 0.0) {
+                    const double z = beta * h;
                     const double z2 = z * z;
                     const double num = (12.0 - 6.0 * z) + z2;
                     const double den = (12.0 + 6.0 * z) + z2;
+                    const double E0 = E;
                     E = E * (num / den);
+                    rated = rated && E == E0;
                 }
                 // stochastic interactions: optical-depth clock
                 tau = S.tau[t] - S.R[t] * h;
                 evt = unpack_flag(S.azf[t]) == LIM_INTER || tau <= 0.0;
                 cycle = true;
             } else {
-                S.nrej[t] += 1u;          // same position: b1 keeps its field
-                double fac = (double)ctrl_k(r) / 1024.0;
-                if (fac < 0.1)
-                    fac = 0.1;
-                h = h * fac;
-                if (h < sp.hmin)
-                    h = sp.hmin;
-                S.azf[t] = (S.azf[t] & 0xffffu) | ((uint32_t)LIM_CTRL << 16);
+                nrejd += 1u;              // same position: b1 keeps its field
+                S.azf[t] = with_flag(S.azf[t], LIM_CTRL);
             }
+            h = hn;   // the retry's step, or the controller's for the next cycle
         }
         if (resume) {
             // the interrupted cycle: its step and loss are done, its
@@ -648,34 +662,33 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
         // slot keeps its state as before the interaction and is parked, to
         // finish the cycle in a later run: nothing is lost
         int chan = CH_NONE;
-        U64x4 w = {{0ull, 0ull, 0ull, 0ull}};
         double dE = 0.0, Esec = 0.0;
-        if (evt) {
-            w = event_draw(sp.seed, S.id[t], S.lineage[t], S.m[t] + 1u);
-            const uint32_t azf = S.azf[t];
-            const Rates ri = species_rates(T, unpack_A(azf), unpack_Z(azf), E);
-            const double Ptot = ri.rpi + ri.rn;
-            chan = !(Ptot > 0.0) ? CH_NULL : (unit_uniform(w.w[0]) * Ptot < ri.rpi ? CH_PI : CH_N);
-        }
         bool defer = false;
         unsigned long long slot_n = 0, slot_pi = 0;
-        {
-            const uint64_t mk = __ballot(chan == CH_N);
-            if (mk) {
+        EventDraw w{0ull, 0.0};
+        if (__ballot(evt) != 0ull) {
+            if (evt) {
+                w = draw<LAYOUT>(opaque(PP)->sp.seed, S.id[t], S.lineage[t], S.m[t] + 1u);
+                const uint32_t azf = S.azf[t];
+                const Rates ri = species_rates(T, unpack_A(azf), unpack_Z(azf), E);
+                const double Ptot = ri.rpi + ri.rn;
+                chan = !(Ptot > 0.0) ? CH_NULL
+                                     : (unit_uniform(w.w0) * Ptot < ri.rpi ? CH_PI : CH_N);
+            }
+            const uint64_t mn = __ballot(chan == CH_N);
+            if (mn) {
                 unsigned long long base = 0;
                 if (lane == 0)
-                    base = atomicAdd(&cnt->tail, (unsigned long long)__popcll(mk));
-                slot_n = __shfl(base, 0) + (unsigned long long)lanes_below(mk);
+                    base = atomicAdd(&cnt->tail, (unsigned long long)__popcll(mn));
+                slot_n = __shfl(base, 0) + (unsigned long long)lanes_below(mn);
                 defer = chan == CH_N && slot_n >= qcap;
             }
-        }
-        {
-            const uint64_t mk = __ballot(chan == CH_PI);
-            if (mk) {
+            const uint64_t mpi = __ballot(chan == CH_PI);
+            if (mpi) {
                 unsigned long long base = 0;
                 if (lane == 0)
-                    base = atomicAdd(&cnt->neu_n, (unsigned long long)__popcll(mk));
-                slot_pi = __shfl(base, 0) + (unsigned long long)lanes_below(mk);
+                    base = atomicAdd(&cnt->neu_n, (unsigned long long)__popcll(mpi));
+                slot_pi = __shfl(base, 0) + (unsigned long long)lanes_below(mpi);
                 defer = defer || (chan == CH_PI &&
                                   slot_pi >= (unsigned long long)opaque(PP)->neu.cap);
             }
@@ -689,12 +702,13 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
             if (evt) {
                 const uint32_t m = S.m[t] + 1u;
                 S.m[t] = m;
+                rated = false;
                 const uint32_t azf = S.azf[t];
                 int A = unpack_A(azf), Z = unpack_Z(azf);
                 const double Eint = E;
                 atomicAdd(&bc[WC_EVENTS], 1ull);
                 if (chan == CH_PI) {
-                    dE = (sp.kappa_pi * Eint) / (double)A;
+                    dE = (opaque(PP)->sp.kappa_pi * Eint) / (double)A;
                     E = Eint - dE;
                     atomicAdd(&bc[WC_PI], 1ull);
                     const NeutralSoA& nq = opaque(PP)->neu;
@@ -715,7 +729,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                     Z -= pout;
                     A -= 1;
                     E = Eint - Esec;
-                    S.azf[t] = pack_azf(A, Z, unpack_flag(azf));
+                    S.azf[t] = pack_azf(A, Z, unpack_flag(azf), unpack_resumed(azf));
                     atomicAdd(&bc[WC_N], 1ull);
                     // the secondary proton: a new candidate in the queue
                     const QueueSoA& q = opaque(PP)->q;
@@ -739,20 +753,20 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                     q.nrej[k] = 0u;
                     q.A[k] = 1;
                     q.Z[k] = 1;
-                    q.tau[k] = optical_depth(event_draw(sp.seed, id, m, 0u).w[1]);
+                    q.tau[k] = draw<LAYOUT>(opaque(PP)->sp.seed, id, m, 0u).tau;
                     __hip_atomic_store(q.ready + k, 1u, __ATOMIC_RELEASE,
                                        __HIP_MEMORY_SCOPE_AGENT);
                 } else {
                     atomicAdd(&bc[WC_NULL], 1ull);
                 }
                 // all interaction state is reset after an interaction
-                tau = optical_depth(w.w[1]);
+                tau = w.tau;
             }
             S.E[t] = E;
             S.tau[t] = tau;
             // boundary and observer modules, checked after the cycle
-            const uint32_t cyc = S.cycles[t] + 1u;
-            S.cycles[t] = cyc;
+            // cycles of this run: its accepted steps and the one resumed, if any
+            const uint32_t cyc = nacc + (uint32_t)unpack_resumed(S.azf[t]);
             if (sp.obs_r > 0.0) {
                 const double d[3] = {x[0] - sp.obs[0], x[1] - sp.obs[1], x[2] - sp.obs[2]};
                 if (sqrt(dot3(d, d)) <= sp.obs_r)
@@ -769,7 +783,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
             if (status == ST_ACTIVE && E < sp.e_floor)
                 status = ST_ENERGY_FLOOR;
             if (status != ST_ACTIVE) {
-                ev |= EV_FIN;
+                fin = true;
                 atomicAdd(&bc[WC_FINISHED], 1ull);
                 atomicAdd(&bc[status == ST_OBSERVED   ? WC_OBSERVED
                               : status == ST_BOUNDARY ? WC_BOUNDARY
@@ -785,12 +799,10 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                 const StepParams& spp = opaque(PP)->sp;
                 const uint32_t every = spp.traj_every;
                 if (every != 0u && S.id[t] < spp.traj_ids)
-                    rec = S.nsteps[t] % every == 0u || status != ST_ACTIVE;
+                    rec = (S.nsteps[t] + nacc) % every == 0u || status != ST_ACTIVE;
             }
             fresh = true;
         }
-        const bool fin = (ev & EV_FIN) != 0u;
-
         // ---- appends: one atomic per wave for each kind ----------------------
         if constexpr (TRAJ) {
             const uint64_t mk = __ballot(rec);
@@ -811,7 +823,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                         tq.E[k] = S.E[t];
                         tq.id[k] = S.id[t];
                         tq.lineage[k] = S.lineage[t];
-                        tq.n[k] = S.nsteps[t];
+                        tq.n[k] = S.nsteps[t] + nacc;
                         tq.A[k] = unpack_A(S.azf[t]);
                     }   // points past the capacity are counted by the host
                 }
@@ -842,8 +854,8 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                         f.id[k] = S.id[t];
                         f.lineage[k] = S.lineage[t];
                         f.m[k] = S.m[t];
-                        f.nsteps[k] = S.nsteps[t];
-                        f.nrej[k] = S.nrej[t];
+                        f.nsteps[k] = S.nsteps[t] + nacc;
+                        f.nrej[k] = S.nrej[t] + nrejd;
                         f.status[k] = status;
                         f.A[k] = unpack_A(S.azf[t]);
                         f.Z[k] = unpack_Z(S.azf[t]);
@@ -874,14 +886,14 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                         pq.E[k] = S.E[t];
                         pq.L[k] = S.L[t];
                         pq.Lmax[k] = S.Lmax[t];
-                        pq.hctrl[k] = S.hctrl[t];
+                        pq.hctrl[k] = h;
                         pq.tau[k] = S.tau[t];
                         pq.E0[k] = Q->q.E0[slot];
                         pq.id[k] = S.id[t];
                         pq.lineage[k] = S.lineage[t];
                         pq.m[k] = S.m[t];
-                        pq.nsteps[k] = S.nsteps[t];
-                        pq.nrej[k] = S.nrej[t];
+                        pq.nsteps[k] = S.nsteps[t] + nacc;
+                        pq.nrej[k] = S.nrej[t] + nrejd;
                         pq.A[k] = unpack_A(S.azf[t]);
                         pq.Z[k] = unpack_Z(S.azf[t]);
                     }
@@ -890,19 +902,19 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
             }
         }
 
-        // ---- bookkeeping: the frequent counts by wave ballot (rare events were
-        // counted with LDS atomics where they happened) ------------------------
-        {
-            const unsigned long long att = count_bit(ev, EV_ATTEMPT);
-            const unsigned long long acc = count_bit(ev, EV_ACCEPT);
-            const unsigned long long frc = count_bit(ev, EV_FORCED);
-            add_count(bc, WC_ATTEMPTS, att);
-            add_count(bc, WC_STEPS, acc);
-            add_count(bc, WC_REJECTS, att - acc);
-            add_count(bc, WC_FORCED, frc);
-            add_count(bc, WC_LANES, 64ull);
+        // ---- bookkeeping of candidates that left their lane ------------------
+        if (fin || park) {
+            atomicAdd(&bc[WC_STEPS], (unsigned long long)nacc);
+            atomicAdd(&bc[WC_REJECTS], (unsigned long long)nrejd);
+            atomicAdd(&bc[WC_ATTEMPTS], (unsigned long long)nacc + nrejd);
+            if (nforced != 0u)
+                atomicAdd(&bc[WC_FORCED], (unsigned long long)nforced);
+            nacc = nrejd = nforced = 0u;
         }
+        ++iters;
     }
+    if (lane == 0)
+        atomicAdd(&bc[WC_LANES], 64ull * iters);
     __syncthreads();   // every wave of the block has left the loop
     flush_counts(cnt, bc);
 }

@@ -252,9 +252,10 @@ GridView make_view(const crp_ctx* ctx)
     g.corner64 = ctx->corner64;
     for (int a = 0; a < 3; ++a) {
         g.n[a] = (int)ctx->gn[a];
-        g.mask[a] = is_pow2(ctx->gn[a]) ? (int)(ctx->gn[a] - 1) : -1;
+        g.inv_n[a] = 1.0 / (double)ctx->gn[a];
         g.origin[a] = ctx->origin[a];
     }
+    g.pow2 = is_pow2(ctx->gn[0]) && is_pow2(ctx->gn[1]) && is_pow2(ctx->gn[2]);
     g.stride[0] = ctx->gn[1] * ctx->gn[2] * 3;
     g.stride[1] = ctx->gn[2] * 3;
     g.stride[2] = 3;
@@ -409,10 +410,8 @@ crp_status ensure_corner(crp_ctx* ctx)
         PatchView& q = ctx->nest.p[k];
         GridView g{};
         g.data = q.data;
-        for (int a = 0; a < 3; ++a) {
+        for (int a = 0; a < 3; ++a)
             g.n[a] = q.n[a];
-            g.mask[a] = is_pow2(q.n[a]) ? q.n[a] - 1 : -1;
-        }
         g.stride[0] = q.stride[0];
         g.stride[1] = q.stride[1];
         g.stride[2] = 3;
