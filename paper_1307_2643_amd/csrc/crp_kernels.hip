@@ -194,6 +194,10 @@ struct FieldOf {
     using T = GridField<GT, LAYOUT>;
 };
 template <class GT>
+struct FieldOf<GT, 0> {
+    using T = LinearKeepField<GT>;
+};
+template <class GT>
 struct FieldOf<GT, 3> {
     using T = NeuralFieldSrc;
 };
@@ -228,7 +232,9 @@ __device__ inline EventDraw draw(uint64_t seed, uint32_t id, uint32_t lineage, u
 
 // 16-byte slots of a wave's LDS staging area.
 template <class GT, int LAYOUT>
-constexpr int stage_float4 = wave_gather<LAYOUT> ? coop_stage_float4<GT> : 0;
+constexpr int stage_float4 = wave_gather<LAYOUT> ? coop_stage_float4<GT>
+                             : LAYOUT == 0       ? keep_float4<GT>
+                                                 : 0;
 
 template <int MODE>
 struct DirType {
@@ -274,7 +280,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
     extern __shared__ __attribute__((aligned(16))) double lds[];
     __shared__ LaneShared<BS> S;              // per-lane cold state
     __shared__ unsigned long long bc[WC_COUNT];   // block bookkeeping counters
-    // the waves' staging areas: the lanes' corner records
+    // the waves' staging areas: the lanes' corner records or kept corner values
     __shared__ float4 stage_mem[stage_float4<GT, LAYOUT> > 0 ? BS / 64 * stage_float4<GT, LAYOUT> : 1];
     // patch table of the multi-resolution grid (LAYOUT 5 only)
     __shared__ PatchView nest_lds[LAYOUT == 5 || LAYOUT == 6 ? MAX_PATCHES : 1];
