@@ -104,6 +104,8 @@ struct PropParams {
     unsigned long long tail0;    // slots below were written before the launch
     unsigned long long fin0;     // finished-record count at the launch
     int refill;                  // idle lanes that trigger a claim (1..64)
+    int lane_cap;                // lanes of a wave that take injected candidates (1..64)
+    int no_append;               // no channel is open: nothing is appended during the run
     NFProp nf;                   // used by the neural-field instantiation only
     AnalyticParams ana;          // used by the analytic-field instantiation only
     NestView nest;               // used by the multi-resolution instantiation only

@@ -337,7 +337,9 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
     const int lane = lane_id();
     const unsigned long long qcap = (unsigned long long)PP->q.cap;
     const unsigned long long tail0 = PP->tail0;
-    const int refill = PP->refill;
+    const int lane_cap = PP->lane_cap;
+    const int refill = min(PP->refill, lane_cap);
+    const bool no_append = PP->no_append != 0;
     const int64_t max_cycles = PP->max_cycles;
     DevCounters* const cnt = PP->cnt;
 
@@ -374,13 +376,19 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
         // ---- refill idle lanes from the queue -------------------------------
         const uint64_t idle = __ballot(!active);
         const int nidle = __popcll(idle);
-        if (idle == ~0ull || nidle >= refill) {
+        // lanes it may fill: up to lane_cap with injected candidates, any with
+        // appended ones, which a wave with work looks for every eighth iteration
+        const int nfree = initial_left ? nidle - (64 - lane_cap) : nidle;
+        bool claim = nfree > 0 && (idle == ~0ull || nfree >= refill);
+        if (!initial_left)
+            claim = claim && !no_append && (idle == ~0ull || (iters & 7u) == 0u);
+        if (claim) {
             const int rank = lanes_below(idle);
             unsigned long long base = 0, take = 0;
             if (initial_left) {
                 bool left = false;
                 if (lane == 0)
-                    claim_initial(cnt, tail0, nidle, base, take, left);
+                    claim_initial(cnt, tail0, nfree, base, take, left);
                 base = __shfl(base, 0);
                 take = __shfl(take, 0);
                 initial_left = __shfl((int)left, 0) != 0;
@@ -398,7 +406,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                 const bool mine = !active && sl < re;
                 bool pub = false;
                 if (mine && sl < qcap)
-                    pub = __hip_atomic_load(opaque(PP)->q.ready + sl, __ATOMIC_ACQUIRE,
+                    pub = __hip_atomic_load(opaque(PP)->q.ready + sl, __ATOMIC_RELAXED,
                                             __HIP_MEMORY_SCOPE_AGENT) != 0u;
                 const uint64_t gap = __ballot(mine && !pub);
                 if (gap)
@@ -407,6 +415,11 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                     take = re - rb < (unsigned long long)nidle ? re - rb : (unsigned long long)nidle;
                 base = rb;
                 rb += take;
+                // the slots' contents are read after their flags; a poll that
+                // finds none does not pay for the acquire, which empties the
+                // compute unit's vector cache
+                if (take != 0ull)
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             }
             if (!active && (unsigned long long)rank < take) {
                 const QueueSoA& q = opaque(PP)->q;
@@ -439,8 +452,11 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
             }
         }
         if (__ballot(active) == 0ull) {
-            // nothing to do: leave once the run has drained, else wait for
-            // secondaries that busy waves may still append
+            // nothing to do: leave once the run has drained (or nothing can be
+            // appended any more), else wait for secondaries that busy waves may
+            // still append
+            if (!initial_left && no_append)
+                break;
             if (!initial_left) {
                 bool drained = false;
                 unsigned long long done = 0;

@@ -79,6 +79,7 @@ struct crp_ctx {
     AnalyticParams ana{};
     double* tab = nullptr;
     int tab_n = 0;
+    bool no_channels = false;      // both channel tables are zero throughout
     float lg0 = 0.0f, lgscale = 0.0f;
 
     // buffers
@@ -560,7 +561,26 @@ crp_status run_kernel(crp_ctx* ctx, int64_t max_cycles, DevCounters* dc)
         else
             bpc = resident_blocks<MODE_MIX, float, 0>(bs, lds);
     }
-    const int nb = ctx->num_cus * bpc;
+    int nb = ctx->num_cus * bpc;
+    // Fewer candidates than lanes of one wave per SIMD (or of the launch's waves,
+    // if those are fewer): spread over these waves instead of packed 64 to a
+    // wave, since an attempt's time grows with the lanes that gather (1000
+    // protons on the 32^3 FP64 grid: 1.13 -> 0.58 ms).  Beyond that they are
+    // packed, as a second wave on a SIMD slows the first.  Where no channel is
+    // open nothing is appended during the run, and the blocks without a candidate
+    // are not launched.  The network stepper's waves cost the same however many
+    // lanes are busy.
+    const int waves_per_block = bs / 64;
+    const int64_t waves = std::min<int64_t>((int64_t)ctx->num_cus * 4,
+                                            (int64_t)nb * waves_per_block);
+    P.lane_cap = 64;
+    if (!neural && ctx->pending < 64 * waves)
+        P.lane_cap = (int)((ctx->pending + waves - 1) / waves);
+    P.no_append = ctx->no_channels ? 1 : 0;
+    if (ctx->no_channels) {
+        const int64_t per_block = (int64_t)P.lane_cap * waves_per_block;
+        nb = (int)std::min<int64_t>(nb, (ctx->pending + per_block - 1) / per_block);
+    }
 
     HIPCHK(ctx, hipMemcpyAsync(ctx->d_params, &P, sizeof P, hipMemcpyHostToDevice, ctx->stream));
     const PropParams* dp = ctx->d_params;
@@ -1214,6 +1234,9 @@ crp_status crp_set_tables(crp_ctx* ctx, int32_t n, const double* e, const double
     HIPCHK(ctx, hipMalloc((void**)&ctx->tab, h.size() * sizeof(double)));
     HIPCHK(ctx, hipMemcpy(ctx->tab, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice));
     ctx->tab_n = n;
+    ctx->no_channels = true;
+    for (int i = 0; i < n; ++i)
+        ctx->no_channels = ctx->no_channels && tpi[i] == 0.0 && tn[i] == 0.0;
     ctx->lg0 = (float)std::log2(e[0]);
     ctx->lgscale = (float)((double)(n - 1) / (std::log2(e[n - 1]) - std::log2(e[0])));
     ctx->has_tables = true;
