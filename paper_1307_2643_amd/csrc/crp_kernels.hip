@@ -384,46 +384,86 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
             claim = claim && !no_append && (idle == ~0ull || (iters & 7u) == 0u);
         if (claim) {
             const int rank = lanes_below(idle);
-            unsigned long long base = 0, take = 0;
-            if (initial_left) {
-                bool left = false;
-                if (lane == 0)
-                    claim_initial(cnt, tail0, nfree, base, take, left);
-                base = __shfl(base, 0);
-                take = __shfl(take, 0);
-                initial_left = __shfl((int)left, 0) != 0;
-            } else {
+            unsigned long long base = 0, take = 0, ibase = 0, itake = 0;
+            // appended candidates first: a long secondary taken up after the
+            // injected ones runs on alone at the end of the launch (1e6 nuclei in
+            // a 512^3 FP32 grid, 3.8e5 secondaries: 164 -> 147 ms)
+            if (!no_append) {
                 if (rb >= re) {
-                    unsigned long long b = 0;
-                    if (lane == 0)
-                        b = atomicAdd(&cnt->head1, (unsigned long long)nidle);
+                    unsigned long long b = 0, want = (unsigned long long)nidle;
+                    if (lane == 0) {
+                        // while injected candidates are left only what is there
+                        if (initial_left) {
+                            unsigned long long tl = __hip_atomic_load(
+                                &cnt->tail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            const unsigned long long hd = __hip_atomic_load(
+                                &cnt->head1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            if (tl > qcap)
+                                tl = qcap;
+                            want = (unsigned long long)nfree;
+                            if (tl < hd + want)
+                                want = tl > hd ? tl - hd : 0ull;
+                        }
+                        if (want != 0ull)
+                            b = atomicAdd(&cnt->head1, want);
+                    }
                     rb = __shfl(b, 0);
-                    re = rb + (unsigned long long)nidle;
+                    re = rb + __shfl(want, 0);
                 }
-                // idle lane of rank r looks at slot rb + r; the published
-                // prefix of the reservation is handed out in order
-                const unsigned long long sl = rb + (unsigned long long)rank;
-                const bool mine = !active && sl < re;
-                bool pub = false;
-                if (mine && sl < qcap)
-                    pub = __hip_atomic_load(opaque(PP)->q.ready + sl, __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_AGENT) != 0u;
-                const uint64_t gap = __ballot(mine && !pub);
-                if (gap)
-                    take = (unsigned long long)__popcll(idle & ((1ull << __builtin_ctzll(gap)) - 1ull));
-                else
-                    take = re - rb < (unsigned long long)nidle ? re - rb : (unsigned long long)nidle;
-                base = rb;
-                rb += take;
-                // the slots' contents are read after their flags; a poll that
-                // finds none does not pay for the acquire, which empties the
-                // compute unit's vector cache
-                if (take != 0ull)
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                if (rb < re) {
+                    // idle lane of rank r looks at slot rb + r; the published
+                    // prefix of the reservation is handed out in order
+                    const unsigned long long sl = rb + (unsigned long long)rank;
+                    const bool mine = !active && sl < re;
+                    bool pub = false;
+                    if (mine && sl < qcap)
+                        pub = __hip_atomic_load(opaque(PP)->q.ready + sl, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT) != 0u;
+                    const uint64_t gap = __ballot(mine && !pub);
+                    if (gap)
+                        take = (unsigned long long)__popcll(
+                            idle & ((1ull << __builtin_ctzll(gap)) - 1ull));
+                    else
+                        take = re - rb < (unsigned long long)nidle ? re - rb
+                                                                   : (unsigned long long)nidle;
+                    base = rb;
+                    rb += take;
+                    // the slots' contents are read after their flags; a poll that
+                    // finds none does not pay for the acquire, which empties the
+                    // compute unit's vector cache
+                    if (take != 0ull)
+                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                }
             }
-            if (!active && (unsigned long long)rank < take) {
+            if (initial_left) {
+                // a lane is kept for each reserved slot that is being written (its
+                // producer publishes it within its iteration; a slot reserved
+                // past the tail may never be)
+                int want = nfree - (int)take;
+                if (rb < re) {
+                    unsigned long long tl = 0;
+                    if (lane == 0)
+                        tl = __hip_atomic_load(&cnt->tail, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                    tl = __shfl(tl, 0);
+                    tl = tl < qcap ? tl : qcap;
+                    tl = tl < re ? tl : re;
+                    want -= tl > rb ? (int)(tl - rb) : 0;
+                }
+                if (want > 0) {
+                    bool left = false;
+                    if (lane == 0)
+                        claim_initial(cnt, tail0, want, ibase, itake, left);
+                    ibase = __shfl(ibase, 0);
+                    itake = __shfl(itake, 0);
+                    initial_left = __shfl((int)left, 0) != 0;
+                }
+            }
+            if (!active && (unsigned long long)rank < take + itake) {
                 const QueueSoA& q = opaque(PP)->q;
-                slot = (int64_t)(base + (unsigned long long)rank);
+                slot = (int64_t)((unsigned long long)rank < take
+                                     ? base + (unsigned long long)rank
+                                     : ibase + ((unsigned long long)rank - take));
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
                     x[a] = q.x[a * q.cap + slot];
