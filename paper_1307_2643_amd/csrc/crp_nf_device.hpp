@@ -113,6 +113,26 @@ __device__ __attribute__((always_inline)) inline void nf_stage_lds(char* dst, co
         d[i] = s[i];
 }
 
+// The same copy straight from memory to LDS (16 bytes per lane and load, no
+// registers): only issued here, so that work that needs no LDS can run under
+// it; the caller's barrier must come after nf_stage_wait().
+__device__ __attribute__((always_inline)) inline void nf_stage_issue(char* dst, const char* src)
+{
+    typedef __attribute__((address_space(3))) void* lds_ptr;
+    const int lane = (int)(threadIdx.x & 63u);
+    const int nw = (int)(blockDim.x >> 6);
+    const int w0 = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    for (int w = w0; w * 1024 < (int)NF_LDS_BYTES; w += nw)
+        if (w * 1024 + 16 * lane < (int)NF_LDS_BYTES)
+            __builtin_amdgcn_global_load_lds((const void*)(src + w * 1024 + 16 * lane),
+                                             (lds_ptr)(dst + w * 1024), 16, 0, 0);
+}
+
+__device__ __attribute__((always_inline)) inline void nf_stage_wait()
+{
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+}
+
 // ReLU as a 32-bit integer maximum with 0: a float is negative exactly when
 // its sign bit is set, i.e. when it is negative as an int32 (-0 included), and
 // non-negative floats order alike, so this is max(v, 0) in one instruction
@@ -157,30 +177,72 @@ __device__ __attribute__((always_inline)) inline void nf_embed(const float* freq
     }
 }
 
+// An FP64 value as the FP32 value of its sign, exponent and upper 20 fraction
+// bits, the last of them set if any bit below was: exact, and rounding it to
+// bf16 (to nearest, ties to even) gives the bf16 rounding of the FP64 value.
+__device__ __attribute__((always_inline)) inline float nf_sticky(double v)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)b;
+    const uint64_t hi = (b >> 32) | (uint64_t)(lo != 0 ? 1u : 0u);
+    return (float)__longlong_as_double((long long)(hi << 32));
+}
+
 // Fourier features for training, in FP64: the phase F . xhat (integer F, FP32
-// xhat: each product exact in FP64) reduced to its fraction in [0, 1) (exact),
-// cos and sin of 2 pi times it by the FP64 library (sincospi), then rounded to
-// bf16.  The features are then within an FP64 rounding of their exact values,
-// so their bf16 roundings are those of the exact features (the stepper's
-// FP32 phase and hardware sin / cos above move a feature by up to ~1e-5).
+// xhat: each product exact in FP64), less the nearest quarter (exact) r in
+// [-1/8, 1/8], the Taylor series of sin and cos of 2 pi r (truncated below
+// 2^-53 of the result), exchanged and signed by the quarter, then rounded to
+// bf16.  The features are within an FP64 rounding or two of their exact values,
+// so their bf16 roundings are those of the exact features (the stepper's FP32
+// phase and hardware sin / cos above move a feature by up to ~1e-5).
+// `freq` in memory: the LDS image may still be on its way.
 __device__ __attribute__((always_inline)) inline void nf_embed_fp64(const float* freq, float x0,
                                                                      float x1, float x2, int g,
                                                                      bf16x8 act[8])
 {
-    freq = nf_launder(freq);
+    // (2 pi)^k / k! with alternating signs
+    constexpr double S[8] = {6.283185307179586, -41.34170224039976, 81.60524927607506,
+                              -76.70585975306139, 42.058693944897655, -15.09464257682299,
+                              3.819952584848282, -0.7181223017785006};
+    constexpr double C[9] = {1.0, -19.739208802178716, 64.9393940226683,
+                              -85.45681720669373, 60.24464137187666, -26.4262567833744,
+                              7.903536371318469, -1.714390711088672, 0.28200596845579123};
+    constexpr double magic = 6755399441055744.0;   // 1.5 2^52: adding it rounds to an integer
     const double d0 = x0, d1 = x1, d2 = x2;
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
+        float f[24];
+#pragma unroll
+        for (int h = 0; h < 6; ++h) {
+            const float4 q = *(const float4*)(freq + 48 * m + 24 * g + 4 * h);
+            f[4 * h] = q.x;
+            f[4 * h + 1] = q.y;
+            f[4 * h + 2] = q.z;
+            f[4 * h + 3] = q.w;
+        }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int jj = 16 * m + 8 * g + j;
-            double ph = ((double)freq[3 * jj] * d0 + (double)freq[3 * jj + 1] * d1) +
-                        (double)freq[3 * jj + 2] * d2;
-            ph = ph - floor(ph);
-            double sv, cv;
-            sincospi(2.0 * ph, &sv, &cv);
-            act[m][j] = (__bf16)cv;
-            act[m + 4][j] = (__bf16)sv;
+            // fused: the products are exact, so the sums round as they would apart
+            const double ph = __builtin_fma((double)f[3 * j + 2], d2,
+                                            __builtin_fma((double)f[3 * j + 1], d1,
+                                                          (double)f[3 * j] * d0));
+            const double y = __builtin_fma(ph, 4.0, magic);
+            const uint32_t q = (uint32_t)__double_as_longlong(y);
+            const double r = __builtin_fma(-0.25, y - magic, ph);
+            const double u = r * r;
+            double sp = S[7], cp = C[8];
+#pragma unroll
+            for (int k = 6; k >= 0; --k)
+                sp = __builtin_fma(sp, u, S[k]);
+#pragma unroll
+            for (int k = 7; k >= 0; --k)
+                cp = __builtin_fma(cp, u, C[k]);
+            const float sf = nf_sticky(sp * r), cf = nf_sticky(cp);
+            const bool odd = (q & 1u) != 0;
+            const uint32_t cv = __float_as_uint(odd ? sf : cf) ^ (((q + 1u) & 2u) << 30);
+            const uint32_t sv = __float_as_uint(odd ? cf : sf) ^ ((q & 2u) << 30);
+            act[m][j] = (__bf16)__uint_as_float(cv);
+            act[m + 4][j] = (__bf16)__uint_as_float(sv);
         }
     }
 }
