@@ -210,19 +210,20 @@ __device__ __forceinline__ uint2 nf_relu_bits(const bf16x8 h[8])
     return r;
 }
 
-__device__ __forceinline__ bool nf_on(const uint2 mk, int m, int j)
+// v where the pattern's bit of (m, j) is set, else +0 (the bit, spread over the
+// word, as a mask: two instructions).
+__device__ __forceinline__ float nf_gate(const uint2 mk, int m, int j, float v)
 {
-    return (((m < 4 ? mk.x : mk.y) >> (8 * (m & 3) + j)) & 1u) != 0;
+    const int on = __builtin_amdgcn_sbfe((int)(m < 4 ? mk.x : mk.y), 8 * (m & 3) + j, 1);
+    return __int_as_float(__float_as_int(v) & on);
 }
 
 constexpr int NF_DBP = 4 * NF_WIDTH + 4;     // per-tile bias sums: dZ_1..dZ_4, dOut, pad
 
-// The training forward gives each wave one 32-point tile (a column block of
-// the MFMA layout) and runs 512-thread blocks: one block per CU (the network
-// image fills the LDS) but two waves per SIMD, whose latencies then hide
-// behind each other's work.  (The backward, whose MFMA chains are denser,
-// measured faster with two column blocks per wave sharing each weight load,
-// as in the stepper's whole-wave evaluation.)
+// The training forward and backward give each wave one 32-point tile (a column
+// block of the MFMA layout) and run 512-thread blocks: one block per CU (the
+// network image fills the LDS) but two waves per SIMD, whose latencies then
+// hide behind each other's work.
 constexpr int NF_TRAIN_BLOCK = 512;
 
 // Training forward, one 32-point tile per wave (points past n repeat point
@@ -337,20 +338,26 @@ __global__ void __launch_bounds__(NF_TRAIN_BLOCK) k_nf_fwd(const char* img, NFGe
 // gradients it stores bf16(dZ_k) in tile order (dz: four layers of
 // [tile][128][32]) and dOut in tile order (dout: [tile][3][32], FP32); for the
 // bias gradients, each tile's sums over its 32 points (dbp: [tile][NF_DBP],
-// dZ_1..dZ_4 by 128 features, then the three outputs).  Two tiles per wave:
-// its 64 lanes hold one point each for dOut, and two column blocks in the
-// layers, so that each weight load from LDS feeds two MFMAs.  The sums take dZ as
+// dZ_1..dZ_4 by 128 features, then the three outputs).  The sums take dZ as
 // bf16(dZ) + bf16(dZ - bf16(dZ)), within 2^-17 of the FP32 value, both parts
 // transposed exactly on the matrix cores.  Adds the loss mean_p |out - tgt|^2
-// (FP64; one atomic per wave) to *loss.
-__global__ void __launch_bounds__(256) k_nf_bwd(const char* img_t, NFGeom G, int64_t n,
-                                                int64_t ld, const float* out, const float* tgt,
-                                                const uint2* relu, __bf16* dz, float* dout,
-                                                float* dbp, double* loss, float inv_n)
+// (FP64) to *loss.
+//
+// Like the forward, one chain per wave at 65536 points, bound by its vector
+// instructions and by waits.  One tile per wave, so two waves per SIMD; all
+// loads of a tile before its first store (vector memory operations complete in
+// order: a load behind the stores waits for them); and one addition to *loss
+// per block -- with one per wave, the additions to the one address held up
+// everything behind them, and two waves per SIMD were slower than one (45.9 us
+// against 36.9 us).  65536 points: 40.7 -> 25.5 us.
+__global__ void __launch_bounds__(NF_TRAIN_BLOCK) k_nf_bwd(const char* img_t, NFGeom G, int64_t n,
+                                                           int64_t ld, const float* out,
+                                                           const float* tgt, const uint2* relu,
+                                                           __bf16* dz, float* dout, float* dbp,
+                                                           double* loss, float inv_n)
 {
     extern __shared__ __attribute__((aligned(16))) char nf_lds[];
-    nf_stage_lds(nf_lds, img_t);
-    __syncthreads();
+    nf_stage_issue(nf_lds, img_t);
     const NFView v = nf_view(nf_lds, G);
     const int lane = (int)(threadIdx.x & 63u);
     const int g = lane >> 5;
@@ -360,12 +367,23 @@ __global__ void __launch_bounds__(256) k_nf_bwd(const char* img_t, NFGeom G, int
     nf_ident(Ilo, Ihi);
     const int64_t wave = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
-    for (int64_t base = wave * 64; base < n; base += nwaves * 64) {
-        const int64_t T0 = base >> 5;
-        // dOut of this lane's own point, in tile order, and its wave sums
+    __shared__ double lred[NF_TRAIN_BLOCK / 64];
+    double lsum = 0.0;          // this lane's squared errors
+    bool first = true;
+    for (int64_t T = wave; first || T * 32 < n; T += nwaves) {
+        if (T * 32 >= n) {
+            nf_stage_wait();
+            __syncthreads();   // no points: only this wave's part of the image
+            break;
+        }
+        // dOut of this lane's point (both groups), in tile order, and its sums
         float d[3] = {0.f, 0.f, 0.f}, dr[3] = {0.f, 0.f, 0.f};
         double sq = 0.0;
-        const int64_t me = base + lane;
+        const int64_t me = T * 32 + rr;
+        // all loads of the tile now: one behind the stores below would wait for them
+        const uint2* pat = relu + T * 64 + lane;
+        const uint2 mk3 = pat[3 * ntile * 64];
+        uint2 mk2 = pat[2 * ntile * 64], mk1 = pat[ntile * 64], mk0 = pat[0];
         if (me < n) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
@@ -376,30 +394,33 @@ __global__ void __launch_bounds__(256) k_nf_bwd(const char* img_t, NFGeom G, int
                 sq += e * e;
             }
         }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1)
-            sq += __shfl_xor(sq, o);
-        if (lane == 0)
-            atomicAdd(loss, sq / (double)n);
+        if (g == 0)
+            lsum += sq;
+        if (first) {
+            // before any store: the wait would include it
+            first = false;
+            nf_stage_wait();
+            __syncthreads();
+        }
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            dout[((T0 + g) * 3 + c) * 32 + nf_tile_pos(rr)] = d[c];
+            if (g == 0)
+                dout[(T * 3 + c) * 32 + nf_tile_pos(rr)] = d[c];
             float s = d[c];
 #pragma unroll
             for (int o = 16; o >= 1; o >>= 1)
                 s += __shfl_xor(s, o);
-            if (rr == 0)
-                dbp[(T0 + g) * NF_DBP + 4 * NF_WIDTH + c] = s;    // tile T0 + g
+            if (lane == 0)
+                dbp[T * NF_DBP + 4 * NF_WIDTH + c] = s;
         }
-        // one hidden layer's gradient tile (k-blocks 2q, 2q + 1 of column
-        // block cb, FP32 values s[16] in result order) kept for the weight and
-        // bias gradients
-        auto keep = [&](int k, int cb, int q, const bf16x8& h0, const bf16x8& h1,
-                        const bf16x8& l0, const bf16x8& l1) {
+        // one hidden layer's gradient tile (k-blocks 2q, 2q + 1, FP32 values in
+        // two bf16 parts) kept for the weight and bias gradients
+        auto keep = [&](int k, int q, const bf16x8& h0, const bf16x8& h1, const bf16x8& l0,
+                        const bf16x8& l1) {
             const floatx16 th = nf_transpose(h0, h1, Ilo, Ihi);
             const floatx16 tl = nf_transpose(l0, l1, Ilo, Ihi);
             nf_store_tile(dz + (int64_t)k * NF_WIDTH * ld +
-                              ((T0 + cb) * NF_WIDTH + 32 * q + rr) * 32 + 16 * g,
+                              (T * NF_WIDTH + 32 * q + rr) * 32 + 16 * g,
                           th);
             float s = 0.0f;
 #pragma unroll
@@ -407,76 +428,78 @@ __global__ void __launch_bounds__(256) k_nf_bwd(const char* img_t, NFGeom G, int
                 s += th[i] + tl[i];
             s += __shfl_xor(s, 32);
             if (g == 0)
-                dbp[(T0 + cb) * NF_DBP + k * NF_WIDTH + 32 * q + rr] = s;
+                dbp[T * NF_DBP + k * NF_WIDTH + 32 * q + rr] = s;
         };
-        bf16x8 dzb[2][8];
+        bf16x8 dzb[8];
         // layer 4: dH4 = W5^T dOut on the vector ALU, then the ReLU mask
-        {
-            const __bf16* w5 = nf_launder(v.w5);
+        const __bf16* w5 = nf_launder(v.w5);
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
-                const int src = 32 * cb + rr;
-                const float d0 = __shfl(dr[0], src), d1 = __shfl(dr[1], src),
-                            d2 = __shfl(dr[2], src);
-                const uint2 mk = relu[((int64_t)3 * ntile + T0 + cb) * 64 + lane];
+        for (int q = 0; q < 4; ++q) {
+            bf16x8 lo[2];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    bf16x8 lo[2];
+            for (int mm = 0; mm < 2; ++mm) {
+                const int m = 2 * q + mm;
+                bf16x8 w[3];
 #pragma unroll
-                    for (int mm = 0; mm < 2; ++mm)
+                for (int c = 0; c < 3; ++c)
+                    w[c] = *(const bf16x8*)(w5 + c * NF_WIDTH + 16 * m + 8 * g);
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            const int m = 2 * q + mm;
-                            const int f = 16 * m + 8 * g + j;
-                            float s = ((float)w5[f] * d0 + (float)w5[NF_WIDTH + f] * d1) +
-                                      (float)w5[2 * NF_WIDTH + f] * d2;
-                            s = nf_on(mk, m, j) ? s : 0.0f;
-                            const __bf16 h = (__bf16)s;
-                            dzb[cb][m][j] = h;
-                            lo[mm][j] = (__bf16)(s - (float)h);
-                        }
-                    keep(3, cb, q, dzb[cb][2 * q], dzb[cb][2 * q + 1], lo[0], lo[1]);
+                for (int j = 0; j < 8; ++j) {
+                    float s = ((float)w[0][j] * dr[0] + (float)w[1][j] * dr[1]) +
+                              (float)w[2][j] * dr[2];
+                    s = nf_gate(mk3, m, j, s);
+                    const __bf16 h = (__bf16)s;
+                    dzb[m][j] = h;
+                    lo[mm][j] = (__bf16)(s - (float)h);
                 }
             }
+            keep(3, q, dzb[2 * q], dzb[2 * q + 1], lo[0], lo[1]);
         }
         // layers 4 -> 1: dH_{k-1} = W_k^T dZ_k, mask with h_{k-1} > 0
 #pragma unroll 1
         for (int k = 3; k >= 1; --k) {
             const __bf16* wimg = nf_launder(v.w[0] + k * NF_IMG_LAYER);
-            const uint2 mk0 = relu[((int64_t)(k - 1) * ntile + T0) * 64 + lane];
-            const uint2 mk1 = relu[((int64_t)(k - 1) * ntile + T0 + 1) * 64 + lane];
-            bf16x8 nxt[2][8];
+            bf16x8 nxt[8];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                floatx16 acc0 = {}, acc1 = {};
+                floatx16 acc = {};
                 const int row = 32 * r + rr;
 #pragma unroll
                 for (int m = 0; m < 8; ++m) {
                     const bf16x8 a = *(const bf16x8*)(wimg + nf_img_off(row, 16 * m + 8 * g));
-                    acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dzb[0][m], acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dzb[1][m], acc1, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dzb[m], acc, 0, 0, 0);
                 }
+                bf16x8 lo[2];
 #pragma unroll
-                for (int cb = 0; cb < 2; ++cb) {
-                    bf16x8 lo[2];
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int m = 2 * r + (i >> 3), j = i & 7;
-                        float s = cb == 0 ? acc0[i] : acc1[i];
-                        s = nf_on(cb == 0 ? mk0 : mk1, m, j) ? s : 0.0f;
-                        const __bf16 h = (__bf16)s;
-                        nxt[cb][m][j] = h;
-                        lo[i >> 3][j] = (__bf16)(s - (float)h);
-                    }
-                    keep(k - 1, cb, r, nxt[cb][2 * r], nxt[cb][2 * r + 1], lo[0], lo[1]);
+                for (int i = 0; i < 16; ++i) {
+                    const int m = 2 * r + (i >> 3), j = i & 7;
+                    const float s = nf_gate(mk2, m, j, acc[i]);
+                    const __bf16 h = (__bf16)s;
+                    nxt[m][j] = h;
+                    lo[i >> 3][j] = (__bf16)(s - (float)h);
                 }
+                keep(k - 1, r, nxt[2 * r], nxt[2 * r + 1], lo[0], lo[1]);
             }
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-                for (int m = 0; m < 8; ++m)
-                    dzb[cb][m] = nxt[cb][m];
+            for (int m = 0; m < 8; ++m)
+                dzb[m] = nxt[m];
+            mk2 = mk1;
+            mk1 = mk0;
         }
+    }
+    // the loss: one addition per block (additions of every wave to the one
+    // address were what the waves waited for)
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1)
+        lsum += __shfl_xor(lsum, o);
+    if (lane == 0)
+        lred[threadIdx.x >> 6] = lsum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w)
+            t += lred[w];
+        atomicAdd(loss, t / (double)n);
     }
 }
 
@@ -947,16 +970,20 @@ static hipError_t nf_fwd_bwd(NeuralField* nf, const NFGeom& G, const GridView& g
 {
     hipStream_t s = nf->stream;
     const int64_t ld = nf->cap;
-    // one 32-point tile per wave, eight waves per block, at most one block per CU
+    // one 32-point tile per wave and at most one block per CU.  Eight waves per
+    // block, but four while those still cover all tiles at once: more CUs then
+    // take part, with a SIMD to each wave (20011 points: forward 24.2 -> 20.8 us,
+    // backward 22.5 -> 19.0 us).
     const int64_t ntl = (n + 31) / 32;
-    int nb = (int)((ntl + NF_TRAIN_BLOCK / 64 - 1) / (NF_TRAIN_BLOCK / 64));
+    const int threads = ntl <= (int64_t)nf->num_cus * 4 ? NF_TRAIN_BLOCK / 2 : NF_TRAIN_BLOCK;
+    int64_t nb = (ntl + threads / 64 - 1) / (threads / 64);
     if (nb > nf->num_cus)
         nb = nf->num_cus;
-    (sample ? k_nf_fwd<true> : k_nf_fwd<false>)<<<nb, NF_TRAIN_BLOCK, NF_LDS_BYTES, s>>>(
+    (sample ? k_nf_fwd<true> : k_nf_fwd<false>)<<<(int)nb, threads, NF_LDS_BYTES, s>>>(
         nf->img_fwd, G, n, ld, nf->xh, g, seed, offset, nf->tgt, nf->acts, nf->relu, nf->out);
-    k_nf_bwd<<<nf_eval_blocks(nf, n), 256, NF_LDS_BYTES, s>>>(nf->img_bwd, G, n, ld, nf->out, nf->tgt, nf->relu,
-                                           nf->dz, nf->dout, nf->dbp, loss,
-                                           (float)(1.0 / (double)n));
+    k_nf_bwd<<<(int)nb, threads, NF_LDS_BYTES, s>>>(nf->img_bwd, G, n, ld, nf->out, nf->tgt,
+                                                    nf->relu, nf->dz, nf->dout, nf->dbp, loss,
+                                                    (float)(1.0 / (double)n));
     // the tiles, split over at most NF_GRAD_CHUNKS chunks of at least 8 tiles
     int64_t chunk = (ntl + NF_GRAD_CHUNKS - 1) / NF_GRAD_CHUNKS;
     if (chunk < 8)
