@@ -533,10 +533,18 @@ __device__ __forceinline__ float nf_sum_strided(const float* p, int64_t stride, 
 // index 8 g + j of step h being tile position 16 g + 8 h + j in both operands
 // (any common order of the points gives the same sums up to rounding).
 // Eight waves: wave w forms row tile w % 4 of a hidden layer's 128 x 128
-// result (column tile w % 4 of the output layer's 3 x 128, rows 3..31 of its
-// tile zero) over the even (w < 4) or odd (w >= 4) tiles of the chunk, with
-// the next tile's operands loaded while the current one's products run; the
-// odd half is added to the even half through LDS.
+// result over the even (w < 4) or odd (w >= 4) tiles of the chunk; the odd half
+// is added to the even half through LDS.  The first wave of each half also
+// forms column tile L of the output layer's 3 x 128 (rows 3..31 of its tile
+// zero).
+//
+// Bound by reading both operands once (151 MB at 65536 points) and, with 32
+// tiles to a block, by how much of that is in flight.  The block's operands go
+// through LDS, each read once from memory (per wave from memory, the four waves
+// of a half read the same input), and are requested two iterations ahead, in
+// registers until the stage is free.  The output layer was a fifth of the
+// blocks, 320 on 256 CUs; as part of the others, 256 blocks run at once.
+// 65536 points: 34.5 -> 27.1 us (5.6 TB/s).
 constexpr int NF_PART_LAYER = NF_WIDTH * NF_WIDTH + NF_WIDTH;
 constexpr int NF_GRAD_CHUNKS = 64;      // point chunks of one gradient launch (at most)
 
@@ -561,123 +569,191 @@ __device__ __forceinline__ bf16x8 nf_cvt8(const float4 lo, const float4 hi)
     return r;
 }
 
-// Operands of one tile for one wave: A (two K-steps) and B (two K-steps of
-// NCT column tiles).
-template <int NCT>
-struct NFTileOps {
-    bf16x8 A[2];
-    bf16x8 B[NCT][2];
+// LDS of one loop iteration: two tiles, of each 128 rows of the layer's
+// gradient and of its input (64 bytes per row), 32 rows of the output layer's
+// input and the three of the output gradient (FP32).
+struct NFGradTile {
+    char a[8192], b[8192], bo[2048], d[512];
+};
+struct NFGradStage {
+    NFGradTile t[2];
 };
 
-template <int NCT>
-__device__ __forceinline__ void nf_wgrad_load(const NFGradIn& in, int L, int64_t T, int wt,
-                                              NFTileOps<NCT>& o)
+// Place of 16-byte chunk q of row r among the rows' chunks: exchanged by the row,
+// so that the 16 rows read together fall on different LDS banks.
+__device__ __forceinline__ int nf_grad_off(int r, int q)
 {
-    const int lane = (int)(threadIdx.x & 63u);
-    const int g = lane >> 5;
-    const int rr = lane & 31;
-    const int64_t pos = 16 * g;
-    if (NCT == 1) {
-        // output layer: A rows are the three outputs (rows 3..31 zero)
-        if (rr < 3) {
-            const float* src = in.dout + (T * 3 + rr) * 32 + pos;
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-                o.A[h] = nf_cvt8(*(const float4*)(src + 8 * h), *(const float4*)(src + 8 * h + 4));
-        } else {
-            o.A[0] = bf16x8{};
-            o.A[1] = bf16x8{};
-        }
-        const __bf16* b = in.a[L] + (T * NF_WIDTH + 32 * wt + rr) * 32 + pos;
-        o.B[0][0] = *(const bf16x8*)b;
-        o.B[0][1] = *(const bf16x8*)(b + 8);
-    } else {
-        const __bf16* a = in.dz[L] + (T * NF_WIDTH + 32 * wt + rr) * 32 + pos;
-        o.A[0] = *(const bf16x8*)a;
-        o.A[1] = *(const bf16x8*)(a + 8);
-#pragma unroll
-        for (int ct = 0; ct < NCT; ++ct) {
-            const __bf16* b = in.a[L] + (T * NF_WIDTH + 32 * ct + rr) * 32 + pos;
-            o.B[ct][0] = *(const bf16x8*)b;
-            o.B[ct][1] = *(const bf16x8*)(b + 8);
-        }
-    }
+    return 64 * r + 16 * (q ^ ((r >> 2) & 3));
 }
 
-template <int NCT>
-__device__ inline void nf_wgrad_block(const NFGradIn& in, int L, int64_t t0, int64_t t1,
-                                      float* red, float* out)
+// A lane's share of one iteration's operands on their way to LDS.
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+struct NFGradRegs {
+    i32x4 v0, v1, v2, v3, v4;
+};
+
+// Where a lane's share of tile 0 lies: 16 rows per load, a wave takes two row
+// groups of its tile's gradient and input each, and waves 0..2 of the tile's
+// four the output layer's (input: two row groups; gradient: 24 chunks).
+struct NFGradSrc {
+    const char *dz, *a, *fifth;
+    int64_t fifth_tile;      // bytes from tile to tile (8192 for the others)
+};
+
+__device__ __forceinline__ NFGradSrc nf_grad_src(const NFGradIn& in, int L, int w)
 {
-    constexpr bool out_layer = NCT == 1;
+    const int lane = (int)(threadIdx.x & 63u);
+    const int p = w & 3;
+    const int at = 64 * (lane >> 2) + 16 * (lane & 3);
+    NFGradSrc s;
+    s.dz = (const char*)in.dz[L] + 2048 * p + at;
+    s.a = (const char*)in.a[L] + 2048 * p + at;
+    s.fifth = p < 2 ? (const char*)in.a[4] + 2048 * L + 1024 * p + at
+                    : (const char*)in.dout + 16 * (lane < 24 ? lane : 0);
+    s.fifth_tile = p < 2 ? 8192 : 384;
+    return s;
+}
+
+// Requests one iteration's operands (tiles T and T + 1, at most t1 - 1).
+__device__ __forceinline__ void nf_grad_load(const NFGradSrc& s, int64_t T, int64_t t1, int w,
+                                             NFGradRegs& o)
+{
+    const int64_t Tk = T + (w >> 2) < t1 ? T + (w >> 2) : t1 - 1;
+    o.v0 = *(const i32x4*)(s.dz + Tk * 8192);
+    o.v1 = *(const i32x4*)(s.dz + Tk * 8192 + 1024);
+    o.v2 = *(const i32x4*)(s.a + Tk * 8192);
+    o.v3 = *(const i32x4*)(s.a + Tk * 8192 + 1024);
+    o.v4 = *(const i32x4*)(s.fifth + Tk * s.fifth_tile);
+}
+
+__device__ __forceinline__ void nf_grad_store(const NFGradRegs& o, int w, NFGradStage& st)
+{
+    const int lane = (int)(threadIdx.x & 63u);
+    const int at = nf_grad_off(lane >> 2, lane & 3);
+    const int p = w & 3;
+    NFGradTile& t = st.t[w >> 2];
+    *(i32x4*)(t.a + 2048 * p + at) = o.v0;
+    *(i32x4*)(t.a + 2048 * p + 1024 + at) = o.v1;
+    *(i32x4*)(t.b + 2048 * p + at) = o.v2;
+    *(i32x4*)(t.b + 2048 * p + 1024 + at) = o.v3;
+    if (p < 2)
+        *(i32x4*)(t.bo + 1024 * p + at) = o.v4;
+    else if (p == 2 && lane < 24)
+        *(i32x4*)(t.d + 16 * lane) = o.v4;
+}
+
+// One tile's products of a wave: row tile wt of the hidden layer, and with wt 0
+// the output layer's column tile.
+__device__ __forceinline__ void nf_grad_products(const NFGradTile& t, int wt, floatx16 acc[4],
+                                                 floatx16& acco)
+{
     const int lane = (int)(threadIdx.x & 63u);
     const int g = lane >> 5;
     const int rr = lane & 31;
-    const int w = (int)(threadIdx.x >> 6);
-    const int wt = w & 3, kg = w >> 2;
-    floatx16 acc[NCT];
 #pragma unroll
-    for (int ct = 0; ct < NCT; ++ct)
-        acc[ct] = floatx16{};
-    int64_t T = t0 + kg;
-    NFTileOps<NCT> cur, nxt;
-    if (T < t1)
-        nf_wgrad_load<NCT>(in, L, T, wt, cur);
-    for (; T < t1; T += 2) {
-        if (T + 2 < t1)
-            nf_wgrad_load<NCT>(in, L, T + 2, wt, nxt);
+    for (int h = 0; h < 2; ++h) {
+        const int at = nf_grad_off(rr, 2 * g + h);
+        const bf16x8 A = *(const bf16x8*)(t.a + 2048 * wt + at);
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int ct = 0; ct < NCT; ++ct)
-                acc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.A[h], cur.B[ct][h], acc[ct],
-                                                                  0, 0, 0);
-        cur = nxt;
+        for (int ct = 0; ct < 4; ++ct)
+            acc[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                A, *(const bf16x8*)(t.b + 2048 * ct + at), acc[ct], 0, 0, 0);
     }
-    // the odd tiles' sums to LDS, added by the wave of the same tile
-    if (kg == 1)
+    if (wt == 0) {
+        // rows 3..31 of the output gradient's operand are zero
+        const float4* d = (const float4*)(t.d + 128 * (rr < 3 ? rr : 0)) + 4 * g;
 #pragma unroll
-        for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                red[((wt * NCT + ct) * 16 + i) * 64 + lane] = acc[ct][i];
-    __syncthreads();
-    if (kg == 0) {
-        // result element i of a lane: row 8 (i / 4) + 4 g + i % 4 of the
-        // tile, column rr
-#pragma unroll
-        for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const float s = acc[ct][i] + red[((wt * NCT + ct) * 16 + i) * 64 + lane];
-                const int r = 8 * (i >> 2) + 4 * g + (i & 3);
-                if (out_layer) {
-                    if (r < 3)
-                        out[r * NF_WIDTH + 32 * wt + rr] = s;
-                } else {
-                    out[(32 * wt + r) * NF_WIDTH + 32 * ct + rr] = s;
-                }
-            }
+        for (int h = 0; h < 2; ++h) {
+            bf16x8 A = nf_cvt8(d[2 * h], d[2 * h + 1]);
+            if (rr >= 3)
+                A = bf16x8{};
+            acco = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                A, *(const bf16x8*)(t.bo + nf_grad_off(rr, 2 * g + h)), acco, 0, 0, 0);
+        }
     }
-    // bias partials: the chunk's per-wave sums in order
-    const int nb = out_layer ? 3 : NF_WIDTH;
-    const int off = out_layer ? 4 * NF_WIDTH : L * NF_WIDTH;
-    for (int f = (int)threadIdx.x; f < nb; f += (int)blockDim.x)
-        out[(out_layer ? 3 : NF_WIDTH) * NF_WIDTH + f] =
-            nf_sum_strided(in.dbp + t0 * NF_DBP + off + f, NF_DBP, (int)(t1 - t0));
 }
 
 __global__ void __launch_bounds__(512) k_nf_wgrad(NFGradIn in, int64_t ntl, int64_t chunk,
                                                   float* part)
 {
-    __shared__ float red[4 * 4 * 16 * 64];
+    __shared__ __attribute__((aligned(16))) NFGradStage s0, s1;
     const int L = (int)blockIdx.y;
     const int64_t t0 = (int64_t)blockIdx.x * chunk;
     const int64_t t1 = t0 + chunk < ntl ? t0 + chunk : ntl;
     float* out = part + ((int64_t)blockIdx.x * 5 + L) * NF_PART_LAYER;
-    if (L == 4)
-        nf_wgrad_block<1>(in, L, t0, t1, red, out);
-    else
-        nf_wgrad_block<4>(in, L, t0, t1, red, out);
+    float* outo = part + ((int64_t)blockIdx.x * 5 + 4) * NF_PART_LAYER;
+    const int lane = (int)(threadIdx.x & 63u);
+    const int g = lane >> 5;
+    const int rr = lane & 31;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int wt = w & 3, kg = w >> 2;
+    floatx16 acc[4], acco = {};
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct)
+        acc[ct] = floatx16{};
+    const NFGradSrc src = nf_grad_src(in, L, w);
+    NFGradRegs r0, r1;
+    nf_grad_load(src, t0, t1, w, r0);
+    nf_grad_load(src, t0 + 2, t1, w, r1);
+    nf_grad_store(r0, w, s0);
+    nf_grad_load(src, t0 + 4, t1, w, r0);
+    for (int64_t T = t0; T < t1; T += 4) {
+        // an iteration reads one stage and fills the one that the iteration
+        // before it read, with operands requested two iterations ago
+        __syncthreads();
+        nf_grad_store(r1, w, s1);
+        nf_grad_load(src, T + 6, t1, w, r1);
+        if (T + kg < t1)
+            nf_grad_products(s0.t[kg], wt, acc, acco);
+        __syncthreads();
+        nf_grad_store(r0, w, s0);
+        nf_grad_load(src, T + 8, t1, w, r0);
+        if (T + 2 + kg < t1)
+            nf_grad_products(s1.t[kg], wt, acc, acco);
+    }
+    // the odd tiles' sums to LDS (16 KB per row tile), added by the wave of the
+    // same tile
+    __syncthreads();
+    float* red = wt < 2 ? (float*)&s0 + 4096 * wt : (float*)&s1 + 4096 * (wt - 2);
+    float* redo = (float*)&s0 + 8192;
+    if (kg == 1) {
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                red[(ct * 16 + i) * 64 + lane] = acc[ct][i];
+        if (wt == 0)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                redo[i * 64 + lane] = acco[i];
+    }
+    __syncthreads();
+    if (kg == 0) {
+        // result element i of a lane: row 8 (i / 4) + 4 g + i % 4 of the
+        // tile, column rr
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int r = 8 * (i >> 2) + 4 * g + (i & 3);
+                out[(32 * wt + r) * NF_WIDTH + 32 * ct + rr] =
+                    acc[ct][i] + red[(ct * 16 + i) * 64 + lane];
+            }
+        if (wt == 0 && g == 0)
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+                outo[r * NF_WIDTH + 32 * L + rr] = acco[r] + redo[r * 64 + lane];
+    } else {
+        // bias partials: the chunk's per-tile sums in order (by the waves that
+        // have nothing to store)
+        const int f = (int)threadIdx.x - 256;
+        if (f < NF_WIDTH)
+            out[NF_WIDTH * NF_WIDTH + f] = nf_sum_strided(
+                in.dbp + t0 * NF_DBP + L * NF_WIDTH + f, NF_DBP, (int)(t1 - t0));
+        else if (L == 0 && f < NF_WIDTH + 3)
+            outo[3 * NF_WIDTH + (f - NF_WIDTH)] = nf_sum_strided(
+                in.dbp + t0 * NF_DBP + 3 * NF_WIDTH + f, NF_DBP, (int)(t1 - t0));
+    }
 }
 
 // Sum of the chunk partials into the flat gradient (W1, b1, ..., W4, b4, W5,
@@ -770,7 +846,7 @@ struct NeuralField {
     __bf16* acts = nullptr;     // five layer inputs, tile order
     __bf16* dz = nullptr;       // four hidden gradients, tile order
     uint2* relu = nullptr;      // ReLU patterns of the hidden outputs
-    float* dbp = nullptr;       // per-wave bias sums
+    float* dbp = nullptr;       // per-tile bias sums
     float* part = nullptr;      // split-K partial gradients [NF_GRAD_CHUNKS][5][NF_PART_LAYER]
     double* loss = nullptr;
     int num_cus = 256;
@@ -996,7 +1072,7 @@ static hipError_t nf_fwd_bwd(NeuralField* nf, const NFGeom& G, const GridView& g
     for (int k = 0; k < 5; ++k)
         gi.a[k] = nf->acts + (int64_t)k * NF_WIDTH * ld;
     gi.dbp = nf->dbp;
-    k_nf_wgrad<<<dim3(*nchunks, 5), 512, 0, s>>>(gi, ntl, chunk, nf->part);
+    k_nf_wgrad<<<dim3(*nchunks, 4), 512, 0, s>>>(gi, ntl, chunk, nf->part);
     return hipGetLastError();
 }
 
