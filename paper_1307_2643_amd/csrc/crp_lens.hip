@@ -190,6 +190,13 @@ template __global__ void k_lens_apply<64>(LensApplyParams);
 // the order of k_lens_apply, so both paths give the same bits.
 constexpr int LENS_GROUP = 16;
 
+// Entries per row, on average, from which eight lanes take an entry.  A row then
+// takes 32 lanes or more, so short rows cost more waves than they save requests:
+// 43008 rows, 16 maps, whole call: 33.5 us with one lane per entry against 34.9 us
+// with eight at 3.3 entries per row, 38.1 against 35.9 us at 5.7, 46.9 against
+// 38.4 us at 11.2; 29.3 against 31.5 us at 0.6.
+constexpr int64_t LENS_SHORT = 4;
+
 __global__ void k_lens_interleave(const double* __restrict__ x, int64_t map_len, int64_t m0,
                                   int nm, double* __restrict__ xt)
 {
@@ -202,10 +209,12 @@ __global__ void k_lens_interleave(const double* __restrict__ x, int64_t map_len,
     }
 }
 
-template <int LPR>
-__global__ void __launch_bounds__(256) k_lens_apply_group(LensApplyParams p, const double* xt,
+// Short rows (fewer than LENS_SHORT entries on average): one lane per entry, four
+// to a row.
+__global__ void __launch_bounds__(256) k_lens_apply_short(LensApplyParams p, const double* xt,
                                                           int64_t m0, int nm)
 {
+    constexpr int LPR = 4;
     const int lane = (int)(threadIdx.x & 63u);
     const int sub = lane & (LPR - 1);
     const int64_t group = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPR;
@@ -240,6 +249,97 @@ __global__ void __launch_bounds__(256) k_lens_apply_group(LensApplyParams p, con
         for (int k = 0; k < LENS_GROUP; ++k)
             if (k < nm)
                 p.y[(m0 + k) * p.map_len + row] = acc[k];
+    }
+}
+
+// Adds to a lane's J partial sums of two maps the next U entries of each (those
+// before e1), all requested before the first is used.
+template <int U, int J, int SLOTS, int LPR>
+__device__ __forceinline__ void lens_entries(const LensApplyParams& p, const double* xr, int64_t b,
+                                             int64_t e1, double acc[J][2])
+{
+    double v[U][J];
+    double2 xv[U][J];
+    bool in[U][J];
+    int32_t c[U][J];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int64_t e = b + LPR * u + SLOTS * j;
+            in[u][j] = e < e1;
+            c[u][j] = p.col[in[u][j] ? e : b];
+            v[u][j] = p.val[in[u][j] ? e : b];
+        }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            xv[u][j] = *(const double2*)(xr + (int64_t)c[u][j] * LENS_GROUP);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            if (in[u][j]) {
+                acc[j][0] += v[u][j] * xv[u][j].x;
+                acc[j][1] += v[u][j] * xv[u][j].y;
+            }
+}
+
+// LPR partial sums per row and map, as in k_lens_apply, but eight lanes to an
+// entry, two maps each: a load instruction covers eight whole lines.  With one
+// lane per entry (64 lines per instruction, eight instructions each) the
+// address unit was the bound; the entries of a partial sum are also requested
+// several at a time.  Row blocks leave their results in LDS, so that a map's
+// values of neighbouring rows are written together.  43008 rows of 11 entries,
+// 16 maps: 21.0 -> 12.9 us.
+template <int LPR>
+__global__ void __launch_bounds__(256) k_lens_apply_group(LensApplyParams p, const double* xt,
+                                                          int64_t m0, int nm)
+{
+    constexpr int SLOTS = LPR < 8 ? LPR : 8;     // entries side by side
+    constexpr int J = LPR / SLOTS;               // partial sums of a lane
+    constexpr int LANES = 8 * SLOTS;             // lanes of a row
+    constexpr int ROWS = 256 / LANES;
+    constexpr int U = J >= 4 ? 1 : 4 / J;        // entries of a partial sum in flight
+    __shared__ double res[LENS_GROUP][ROWS];
+    const int t = (int)threadIdx.x;
+    const int r = t / LANES, slot = t / 8 % SLOTS, h = t % 8;
+    const int64_t row = (int64_t)blockIdx.x * ROWS + r;
+    double acc[J][2];
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+        acc[j][0] = acc[j][1] = 0.0;
+    if (row < p.nrows) {
+        // first column of this rigidity's block, this lane's pair of maps
+        const double* xr = xt + row / p.npix * p.npix * LENS_GROUP + 2 * h;
+        const int64_t e1 = p.rowptr[row + 1];
+        for (int64_t b = p.rowptr[row] + slot; b < e1; b += LPR * U)
+            lens_entries<U, J, SLOTS, LPR>(p, xr, b, e1, acc);
+    }
+    // partial sums SLOTS j + slot, paired at distances LPR / 2 ... 1
+#pragma unroll
+    for (int o = J / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int j = 0; j < o; ++j) {
+            acc[j][0] += acc[j + o][0];
+            acc[j][1] += acc[j + o][1];
+        }
+#pragma unroll
+    for (int o = SLOTS / 2; o > 0; o >>= 1) {
+        acc[0][0] += __shfl_xor(acc[0][0], 8 * o);
+        acc[0][1] += __shfl_xor(acc[0][1], 8 * o);
+    }
+    if (slot == 0) {
+        res[2 * h][r] = acc[0][0];
+        res[2 * h + 1][r] = acc[0][1];
+    }
+    __syncthreads();
+    if (t < LENS_GROUP * ROWS) {
+        const int k = t / ROWS;
+        const int64_t i = (int64_t)blockIdx.x * ROWS + t % ROWS;
+        if (k < nm && i < p.nrows)
+            p.y[(m0 + k) * p.map_len + i] = res[k][t % ROWS];
     }
 }
 
@@ -424,12 +524,16 @@ hipError_t lens_apply(Lens& L, int n_maps, const double* x, double* y, hipStream
                 return e;
             L.xt_cap = need;
         }
-        const unsigned nb = (unsigned)((L.nrows * L.lpr + 255) / 256);
+        const bool brief = L.nnz < LENS_SHORT * L.nrows;
+        const int rows = brief ? 64 : L.lpr == 4 ? 8 : 4;     // of a block
+        const unsigned nb = (unsigned)((L.nrows + rows - 1) / rows);
         const int ib = (int)std::min<int64_t>((need + 255) / 256, 65536);
         for (int64_t m0 = 0; m0 < n_maps; m0 += LENS_GROUP) {
             const int nm = (int)std::min<int64_t>(LENS_GROUP, n_maps - m0);
             k_lens_interleave<<<ib, 256, 0, s>>>(x, L.nrows, m0, nm, L.xt);
-            switch (L.lpr) {
+            // (rows this short have lpr 4: the same sums)
+            switch (brief ? 0 : L.lpr) {
+            case 0: k_lens_apply_short<<<nb, 256, 0, s>>>(p, L.xt, m0, nm); break;
             case 4: k_lens_apply_group<4><<<nb, 256, 0, s>>>(p, L.xt, m0, nm); break;
             case 8: k_lens_apply_group<8><<<nb, 256, 0, s>>>(p, L.xt, m0, nm); break;
             case 16: k_lens_apply_group<16><<<nb, 256, 0, s>>>(p, L.xt, m0, nm); break;
