@@ -842,6 +842,7 @@ struct NeuralField {
     int64_t t = 0;              // Adam step
     // training buffers
     int64_t cap = 0;
+    double* pos = nullptr;      // caller-given points
     float *xh = nullptr, *tgt = nullptr, *out = nullptr, *dout = nullptr;
     __bf16* acts = nullptr;     // five layer inputs, tile order
     __bf16* dz = nullptr;       // four hidden gradients, tile order
@@ -856,11 +857,12 @@ struct NeuralField {
 
 static void nf_free_train(NeuralField* nf)
 {
-    for (void* p : {(void*)nf->xh, (void*)nf->tgt, (void*)nf->out, (void*)nf->dout,
+    for (void* p : {(void*)nf->pos, (void*)nf->xh, (void*)nf->tgt, (void*)nf->out, (void*)nf->dout,
                     (void*)nf->acts, (void*)nf->dz, (void*)nf->relu, (void*)nf->dbp,
                     (void*)nf->part})
         if (p)
             (void)hipFree(p);
+    nf->pos = nullptr;
     nf->xh = nf->tgt = nf->out = nf->dout = nf->dbp = nf->part = nullptr;
     nf->acts = nf->dz = nullptr;
     nf->relu = nullptr;
@@ -1022,6 +1024,7 @@ static hipError_t nf_ensure_cap(NeuralField* nf, int64_t n)
         if (e == hipSuccess)
             e = hipMalloc(p, b);
     };
+    al((void**)&nf->pos, ld * 24);
     al((void**)&nf->xh, ld * 12);
     al((void**)&nf->tgt, ld * 12);
     al((void**)&nf->out, ld * 12);
@@ -1111,15 +1114,12 @@ crp_status nf_loss_grad(NeuralField* nf, const GridView& g, int64_t n, const dou
     hipStream_t s = nf->stream;
     hipError_t e = nf_ensure_cap(nf, n);
     const NFGeom G = nf_geom(nf, g);
-    double* dpos = nullptr;
     if (e == hipSuccess)
-        e = hipMalloc((void**)&dpos, n * 24);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(dpos, pos, n * 24, hipMemcpyHostToDevice, s);
+        e = hipMemcpyAsync(nf->pos, pos, n * 24, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(nf->tgt, target, n * 12, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
-        k_nf_xhat<<<(int)((n + 255) / 256), 256, 0, s>>>(G, n, dpos, nf->xh);
+        k_nf_xhat<<<(int)((n + 255) / 256), 256, 0, s>>>(G, n, nf->pos, nf->xh);
         e = hipGetLastError();
     }
     int nchunks = 0;
@@ -1140,8 +1140,6 @@ crp_status nf_loss_grad(NeuralField* nf, const GridView& g, int64_t n, const dou
         e = hipMemcpyAsync(&l, nf->loss, 8, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess)
         e = hipStreamSynchronize(s);
-    if (dpos)
-        (void)hipFree(dpos);
     if (e != hipSuccess) {
         err = std::string("nf_loss_grad: ") + hipGetErrorString(e);
         return e == hipErrorOutOfMemory ? CRP_ENOMEM : CRP_EDEVICE;
