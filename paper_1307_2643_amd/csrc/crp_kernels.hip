@@ -387,8 +387,13 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
             unsigned long long base = 0, take = 0, ibase = 0, itake = 0;
             // appended candidates first: a long secondary taken up after the
             // injected ones runs on alone at the end of the launch (1e6 nuclei in
-            // a 512^3 FP32 grid, 3.8e5 secondaries: 164 -> 147 ms)
-            if (!no_append) {
+            // a 512^3 FP32 grid, 3.8e5 secondaries: 164 -> 147 ms).  A wave with
+            // work looks for them every eighth iteration only: the look is two
+            // dependent loads of contended counters, and taking a few at a time an
+            // acquire (looking at every claim: 147 against 133 ms there; 1e7 in a
+            // 1024^3 grid, refill 4, 1103 against 989 ms, before either 1048 ms)
+            if (!no_append &&
+                (!initial_left || rb < re || idle == ~0ull || (iters & 7u) == 0u)) {
                 if (rb >= re) {
                     unsigned long long b = 0, want = (unsigned long long)nidle;
                     if (lane == 0) {
