@@ -1468,6 +1468,15 @@ crp_status crp_inject(crp_ctx* ctx, int64_t n, const uint32_t* id, const int32_t
     const double *d_E = E, *d_pos = pos, *d_dir = dir, *d_lmax = lmax;
     void* stage = nullptr;      // to be freed
     char* d_stage = nullptr;
+    // Ends the upload of host arrays: a staging buffer of this call is freed (which
+    // waits), and no copy out of the context's pinned memory stays under way, since
+    // the next call writes there.
+    auto end_upload = [&] {
+        if (stage)
+            (void)hipFree(stage);
+        else if (d_stage)
+            (void)hipStreamSynchronize(ctx->stream);
+    };
     if (!on_device) {
         for (int64_t i = 0; i < n; ++i) {
             bool ok = A[i] >= 1 && A[i] <= 255 && Z[i] >= 1 && Z[i] <= A[i] &&
@@ -1519,8 +1528,7 @@ crp_status crp_inject(crp_ctx* ctx, int64_t n, const uint32_t* id, const int32_t
         if (small)
             e = hipMemcpyAsync(d_stage, small, cv.off, hipMemcpyHostToDevice, ctx->stream);
         if (e != hipSuccess) {
-            if (stage)
-                (void)hipFree(stage);
+            end_upload();
             return fail(ctx, CRP_EDEVICE, std::string("inject upload: ") + hipGetErrorString(e));
         }
         d_id = s_id;
@@ -1547,8 +1555,7 @@ crp_status crp_inject(crp_ctx* ctx, int64_t n, const uint32_t* id, const int32_t
     if (ctx->cfg.inject_order == CRP_ORDER_LONGEST_FIRST && n > 1 && n <= INT32_MAX) {
         const crp_status st = inject_order_perm(ctx, n, d_Z, d_E, d_lmax, &perm);
         if (st != CRP_OK) {
-            if (stage)
-                (void)hipFree(stage);
+            end_upload();
             return st;
         }
     }
@@ -1558,8 +1565,8 @@ crp_status crp_inject(crp_ctx* ctx, int64_t n, const uint32_t* id, const int32_t
     hipError_t e = hipGetLastError();
     if (e == hipSuccess)
         e = hipStreamSynchronize(ctx->stream);
-    if (stage)
-        (void)hipFree(stage);
+    if (stage || e != hipSuccess)
+        end_upload();
     if (e != hipSuccess)
         return fail(ctx, CRP_EDEVICE, std::string("inject: ") + hipGetErrorString(e));
     ctx->pending += n;

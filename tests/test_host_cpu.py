@@ -1,0 +1,38 @@
+"""Host code of libcrp.so on the CPU, its HIP calls answered by tests/host/fake_hip.hpp."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    """Compiles tests/host/NAME.cpp against libcrp.so and returns its path."""
+    from paper_1307_2643_amd import build as B
+    pkg = os.path.dirname(B.LIB)
+    out = tmp_path_factory.mktemp("host")
+
+    def make(name):
+        exe = out / name
+        if not exe.exists():
+            subprocess.check_call(
+                [B.hipcc(), "--offload-arch=" + B.ARCH, "--offload-host-only", "-x", "hip",
+                 "-std=c++17", "-O1", "-rdynamic", "-I", os.path.join(pkg, "..", "include"), "-I",
+                 os.path.join(pkg, "csrc"), os.path.join(HERE, "host", name + ".cpp"), "-x", "none",
+                 B.LIB, "-Wl,-rpath," + pkg, "-o", str(exe)])
+        return str(exe)
+    return make
+
+
+def run(exe, *args):
+    r = subprocess.run([exe, *args], capture_output=True, text=True, timeout=120)
+    print(r.stdout + r.stderr)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
+
+
+@pytest.mark.parametrize("kernel", ["k_inject_keys", "8k_inject"])
+def test_failed_injection_waits_for_its_upload(driver, kernel):
+    run(driver("inject_failure"), kernel)
