@@ -130,7 +130,8 @@ typedef struct {
                                  as many as the kernel's occupancy lets one
                                  compute unit hold at once */
     int32_t refill;           /* a wave claims new candidates once this many of its
-                                 64 lanes are idle (1..64) */
+                                 64 lanes are idle (1..64; at most the lanes that
+                                 a spread batch uses of a wave, see crp_set_launch) */
     int32_t layout;           /* CRP_LAYOUT_LINEAR or CRP_LAYOUT_CORNER */
 } crp_launch;
 
@@ -419,7 +420,12 @@ crp_status crp_eval_field_noalloc(crp_ctx* ctx, int64_t n, const double* pos_m, 
  * at most 2^32 - 1 cells): 128 bytes per cell for an FP32 grid (24 floats and
  * a pad), 192 bytes for an FP64 grid (24 doubles).  The field values read are
  * the same in either layout, so results do not depend on it.  An FP64 grid
- * with refinement patches is read from the linear arrays in either layout. */
+ * with refinement patches is read from the linear arrays in either layout.
+ * A batch of fewer candidates than four waves per compute unit have lanes (or
+ * than the launch has, if those are fewer) is spread: every wave takes its share
+ * of them, ceil(candidates / waves) lanes, and refill is at most that; with tables
+ * whose channels are all zero, blocks without a candidate are not launched.  The
+ * neural-field stepper is not spread. */
 crp_status crp_set_launch(crp_ctx* ctx, const crp_launch* launch);
 crp_status crp_get_launch(crp_ctx* ctx, crp_launch* launch);
 
@@ -432,7 +438,8 @@ crp_status crp_get_launch(crp_ctx* ctx, crp_launch* launch);
  * 1 and 64 and 2 blocks per compute unit.  The trials run on a copy of the
  * pending queue (restored after each trial, so the
  * pending work is unchanged) run for max_cycles cycles (<= 0: to completion),
- * keeps the fastest in the context and appends it to cache_path (NULL: no
+ * launched with full waves and all blocks as a large batch is, even if the
+ * pending work is few; keeps the fastest in the context and appends it to cache_path (NULL: no
  * file) under a key of (device name, grid shape, dtype, precision, field
  * mode).  If cache_path already holds an entry for this key, its latest shape
  * is taken without trials.  best_rate: accepted steps per second of the chosen

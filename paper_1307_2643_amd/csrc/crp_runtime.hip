@@ -564,8 +564,10 @@ void free_corner(crp_ctx* ctx)
 }
 
 // Launches one propagation run over the pending queue (no host bookkeeping
-// of totals).  On return the device counter block is in *dc.
-crp_status run_kernel(crp_ctx* ctx, int64_t max_cycles, DevCounters* dc)
+// of totals).  On return the device counter block is in *dc.  spread: a small batch
+// is spread over the waves (below); the autotuner's trials are not, so that the
+// shape it times is the one that a large batch gets.
+crp_status run_kernel(crp_ctx* ctx, int64_t max_cycles, DevCounters* dc, bool spread = true)
 {
     DevCounters init;
     std::memset(&init, 0, sizeof init);
@@ -685,10 +687,10 @@ crp_status run_kernel(crp_ctx* ctx, int64_t max_cycles, DevCounters* dc)
     const int64_t waves = std::min<int64_t>((int64_t)ctx->num_cus * 4,
                                             (int64_t)nb * waves_per_block);
     P.lane_cap = 64;
-    if (!neural && ctx->pending < 64 * waves)
+    if (spread && !neural && ctx->pending < 64 * waves)
         P.lane_cap = (int)((ctx->pending + waves - 1) / waves);
     P.no_append = ctx->no_channels ? 1 : 0;
-    if (ctx->no_channels) {
+    if (spread && ctx->no_channels) {
         const int64_t per_block = (int64_t)P.lane_cap * waves_per_block;
         nb = (int)std::min<int64_t>(nb, (ctx->pending + per_block - 1) / per_block);
     }
@@ -2224,7 +2226,7 @@ crp_status crp_tune(crp_ctx* ctx, int64_t max_cycles, const char* cache_path, cr
             ctx->traj_unread = traj0;
             ctx->launch = l;
             DevCounters dc;
-            st = run_kernel(ctx, max_cycles, &dc);
+            st = run_kernel(ctx, max_cycles, &dc, false);
             if (st != CRP_OK)
                 break;
             const double rate =

@@ -36,3 +36,7 @@ def run(exe, *args):
 @pytest.mark.parametrize("kernel", ["k_inject_keys", "8k_inject"])
 def test_failed_injection_waits_for_its_upload(driver, kernel):
     run(driver("inject_failure"), kernel)
+
+
+def test_tuner_trials_are_launched_as_large_batches(driver):
+    run(driver("tune"), "trials")
