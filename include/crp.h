@@ -439,8 +439,9 @@ crp_status crp_get_launch(crp_ctx* ctx, crp_launch* launch);
  * pending queue (restored after each trial, so the
  * pending work is unchanged) run for max_cycles cycles (<= 0: to completion),
  * launched with full waves and all blocks as a large batch is, even if the
- * pending work is few; keeps the fastest in the context and appends it to cache_path (NULL: no
- * file) under a key of (device name, grid shape, dtype, precision, field
+ * pending work is few; keeps the fastest in the context (one with fewer blocks
+ * per compute unit than fit only if it is faster by more than 3%, which is the
+ * trials' noise) and appends it to cache_path (NULL: no file) under a key of (device name, grid shape, dtype, precision, field
  * mode).  If cache_path already holds an entry for this key, its latest shape
  * is taken without trials.  best_rate: accepted steps per second of the chosen
  * shape (from the cache when taken from it).  Needs pending work unless the

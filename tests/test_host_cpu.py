@@ -40,3 +40,10 @@ def test_failed_injection_waits_for_its_upload(driver, kernel):
 
 def test_tuner_trials_are_launched_as_large_batches(driver):
     run(driver("tune"), "trials")
+
+
+@pytest.mark.parametrize("percent,kept", [(1.5, "128 0"), (-1.5, "128 0"), (5.0, "128 3")])
+def test_tuner_takes_fewer_waves_only_beyond_the_noise(driver, percent, kept):
+    """Three blocks per compute unit instead of the filled unit: kept when they are faster by
+    more than the calibration's noise (3 percent), not within it."""
+    assert f"kept {kept}\n" in run(driver("tune"), "keep", str(percent))
