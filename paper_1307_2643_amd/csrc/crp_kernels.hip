@@ -151,12 +151,17 @@ constexpr uint32_t IDLE_SLEEP_LIMIT = 1u << 23;
 
 // Per-lane candidate state that is not needed inside a Cash-Karp attempt,
 // kept in LDS (structure of arrays over the block's lanes) so that only the
-// position, direction, step and curvature occupy registers in the attempt.
+// position, direction, step and curvature occupy registers in the attempt.  What
+// only the candidate's end asks for (E0, u0, its counts before this run) is read
+// from its queue slot again, and the lineage has a register (the linear layout,
+// whose registers are full, reads it again too): with these here, 72 bytes a lane,
+// two blocks of 256 on FP32 corner records did not fit a compute unit with more than
+// 948 table nodes (1e6 candidates in a 256^3 grid with a patch, 1024 nodes: 287 ms;
+// now 190 ms, as with 200 nodes).
 template <int BS>
 struct LaneShared {
     double E[BS], L[BS], Lmax[BS], tau[BS], R[BS], beta[BS];
-    uint32_t id[BS], lineage[BS], m[BS];
-    uint32_t nsteps[BS], nrej[BS];   // as claimed (without this run's counts)
+    uint32_t id[BS], m[BS];
     uint32_t azf[BS];   // A | Z << 8 | step-limit flag << 16 | claimed to resume << 24
 };
 
@@ -352,6 +357,14 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
     // S.R, S.beta and kappa belong to the candidate's present species and energy
     bool rated = false;
     uint32_t nacc = 0u, nrejd = 0u, nforced = 0u;   // this candidate's counts in this run
+    uint32_t lineage_reg = 0u;
+    uint32_t nclaimed = 0u;                         // TRAJ: its steps before this run
+    auto lineage = [&]() -> uint32_t {
+        if constexpr (LAYOUT != 0)
+            return lineage_reg;
+        else
+            return opaque(PP)->q.lineage[slot];
+    };
     uint64_t iters = 0;                             // attempts of the wave
     // the lane holds a candidate whose last cycle stopped just before an
     // interaction for want of an output slot: it finishes that cycle first
@@ -480,10 +493,11 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                 h = q.hctrl[slot];
                 S.tau[t] = q.tau[slot];
                 S.id[t] = q.id[slot];
-                S.lineage[t] = q.lineage[slot];
                 S.m[t] = q.m[slot];
-                S.nsteps[t] = q.nsteps[slot];
-                S.nrej[t] = q.nrej[slot];
+                if constexpr (LAYOUT != 0)
+                    lineage_reg = q.lineage[slot];
+                if constexpr (TRAJ)
+                    nclaimed = q.nsteps[slot];
                 resume = S.tau[t] < 0.0;
                 // a resumed cycle keeps the step limit its step had
                 S.azf[t] = pack_azf(q.A[slot], q.Z[slot],
@@ -735,7 +749,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
         EventDraw w{0ull, 0.0};
         if (__ballot(evt) != 0ull) {
             if (evt) {
-                w = draw<LAYOUT>(opaque(PP)->sp.seed, S.id[t], S.lineage[t], S.m[t] + 1u);
+                w = draw<LAYOUT>(opaque(PP)->sp.seed, S.id[t], lineage(), S.m[t] + 1u);
                 const uint32_t azf = S.azf[t];
                 const Rates ri = species_rates(T, unpack_A(azf), unpack_Z(azf), E);
                 const double Ptot = ri.rpi + ri.rn;
@@ -787,7 +801,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                     }
                     nq.E[k] = dE;
                     nq.id[k] = S.id[t];
-                    nq.lineage[k] = S.lineage[t];
+                    nq.lineage[k] = lineage();
                     nq.m[k] = m;
                     nq.chan[k] = 0;
                 } else if (chan == CH_N) {
@@ -866,7 +880,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                 const StepParams& spp = opaque(PP)->sp;
                 const uint32_t every = spp.traj_every;
                 if (every != 0u && S.id[t] < spp.traj_ids)
-                    rec = (S.nsteps[t] + nacc) % every == 0u || status != ST_ACTIVE;
+                    rec = (nclaimed + nacc) % every == 0u || status != ST_ACTIVE;
             }
             fresh = true;
         }
@@ -889,8 +903,8 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                         tq.L[k] = S.L[t];
                         tq.E[k] = S.E[t];
                         tq.id[k] = S.id[t];
-                        tq.lineage[k] = S.lineage[t];
-                        tq.n[k] = S.nsteps[t] + nacc;
+                        tq.lineage[k] = lineage();
+                        tq.n[k] = nclaimed + nacc;
                         tq.A[k] = unpack_A(S.azf[t]);
                     }   // points past the capacity are counted by the host
                 }
@@ -909,6 +923,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                     if (i < (unsigned long long)Q->fin.cap) {
                         const FinishedSoA& f = Q->fin;
                         const int64_t k = (int64_t)i;
+                        const uint32_t ns = Q->q.nsteps[slot], nr = Q->q.nrej[slot];
 #pragma unroll
                         for (int a = 0; a < 3; ++a) {
                             f.x[a * f.cap + k] = x[a];
@@ -919,10 +934,10 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                         f.L[k] = S.L[t];
                         f.E0[k] = Q->q.E0[slot];
                         f.id[k] = S.id[t];
-                        f.lineage[k] = S.lineage[t];
+                        f.lineage[k] = lineage();
                         f.m[k] = S.m[t];
-                        f.nsteps[k] = S.nsteps[t] + nacc;
-                        f.nrej[k] = S.nrej[t] + nrejd;
+                        f.nsteps[k] = ns + nacc;
+                        f.nrej[k] = nr + nrejd;
                         f.status[k] = status;
                         f.A[k] = unpack_A(S.azf[t]);
                         f.Z[k] = unpack_Z(S.azf[t]);
@@ -944,6 +959,7 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                     if (i < (unsigned long long)Q->park.cap) {
                         const QueueSoA& pq = Q->park;
                         const int64_t k = (int64_t)i;
+                        const uint32_t ns = Q->q.nsteps[slot], nr = Q->q.nrej[slot];
 #pragma unroll
                         for (int a = 0; a < 3; ++a) {
                             pq.x[a * pq.cap + k] = x[a];
@@ -957,10 +973,10 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
                         pq.tau[k] = S.tau[t];
                         pq.E0[k] = Q->q.E0[slot];
                         pq.id[k] = S.id[t];
-                        pq.lineage[k] = S.lineage[t];
+                        pq.lineage[k] = lineage();
                         pq.m[k] = S.m[t];
-                        pq.nsteps[k] = S.nsteps[t] + nacc;
-                        pq.nrej[k] = S.nrej[t] + nrejd;
+                        pq.nsteps[k] = ns + nacc;
+                        pq.nrej[k] = nr + nrejd;
                         pq.A[k] = unpack_A(S.azf[t]);
                         pq.Z[k] = unpack_Z(S.azf[t]);
                     }
