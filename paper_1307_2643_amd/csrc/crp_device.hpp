@@ -336,8 +336,10 @@ __device__ inline Cell locate(const GridView& g, const double p[3])
     return c;
 }
 
-// The 8 corner vectors of a cell in the order c = dx + 2 dy + 4 dz.
-template <class GT>
+// The 8 corner vectors of a cell in the order c = dx + 2 dy + 4 dz.  EDGES: the two
+// ends of a z-edge, which share a 128-byte line in most cells, are loaded one after
+// the other.
+template <class GT, bool EDGES = false>
 __device__ inline void gather_linear(const GridView& g, const Cell& c, GT v[8][3])
 {
     const GT* G = (const GT*)g.data;
@@ -345,7 +347,8 @@ __device__ inline void gather_linear(const GridView& g, const Cell& c, GT v[8][3
     const int64_t oy[2] = {(int64_t)c.i0[1] * g.stride[1], (int64_t)c.i1[1] * g.stride[1]};
     const int64_t oz[2] = {(int64_t)c.i0[2] * 3, (int64_t)c.i1[2] * 3};
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int i = 0; i < 8; ++i) {
+        const int k = EDGES ? (i >> 1) + 4 * (i & 1) : i;
         const GT* p = G + ox[k & 1] + oy[(k >> 1) & 1] + oz[(k >> 2) & 1];
         v[k][0] = p[0];
         v[k][1] = p[1];
@@ -512,40 +515,52 @@ __device__ inline int64_t cell_index(const GridView& g, const Cell& c)
 }
 
 // FP64 weights and sums: w0 = 1 - t, w1 = t; weight (wx * wy) * wz.
-template <class GT>
-__device__ inline void interp_fp64(const double t[3], const GT v[8][3], double B[3])
+template <int K0, int K1, class GT>
+__device__ inline void interp_fp64_part(const double t[3], const GT v[K1 - K0][3], double B[3])
 {
     const double wx[2] = {1.0 - t[0], t[0]};
     const double wy[2] = {1.0 - t[1], t[1]};
     const double wz[2] = {1.0 - t[2], t[2]};
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = K0; k < K1; ++k) {
         const double w = (wx[k & 1] * wy[(k >> 1) & 1]) * wz[(k >> 2) & 1];
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-            const double term = w * (double)v[k][q];
+            const double term = w * (double)v[k - K0][q];
             B[q] = k == 0 ? term : B[q] + term;
         }
     }
 }
 
-// FP32 weights and sums (precision form); t is rounded to FP32 first.
 template <class GT>
-__device__ inline void interp_fp32(const double t[3], const GT v[8][3], float B[3])
+__device__ inline void interp_fp64(const double t[3], const GT v[8][3], double B[3])
+{
+    interp_fp64_part<0, 8>(t, v, B);
+}
+
+// FP32 weights and sums (precision form); t is rounded to FP32 first.
+template <int K0, int K1, class GT>
+__device__ inline void interp_fp32_part(const double t[3], const GT v[K1 - K0][3], float B[3])
 {
     const float tx = (float)t[0], ty = (float)t[1], tz = (float)t[2];
     const float wx[2] = {1.0f - tx, tx};
     const float wy[2] = {1.0f - ty, ty};
     const float wz[2] = {1.0f - tz, tz};
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = K0; k < K1; ++k) {
         const float w = (wx[k & 1] * wy[(k >> 1) & 1]) * wz[(k >> 2) & 1];
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-            const float term = w * (float)v[k][q];
+            const float term = w * (float)v[k - K0][q];
             B[q] = k == 0 ? term : B[q] + term;
         }
     }
+}
+
+template <class GT>
+__device__ inline void interp_fp32(const double t[3], const GT v[8][3], float B[3])
+{
+    interp_fp32_part<0, 8>(t, v, B);
 }
 
 // The corner values of the cell each lane gathered last, kept in the wave's
@@ -570,13 +585,14 @@ __device__ inline void keep_write(float* stage, const GT v[8][3])
     }
 }
 
+// Corners 4 h to 4 h + 3 of the cell.
 template <class GT>
-__device__ inline void keep_read(const float* stage, GT v[8][3])
+__device__ inline void keep_read(const float* stage, int h, GT v[4][3])
 {
     constexpr int EPC = 16 / (int)sizeof(GT);
-    const char* my = (const char*)stage + 16 * (threadIdx.x & 63u);
+    const char* my = (const char*)stage + 16 * (threadIdx.x & 63u) + h * (1024 * 12 / EPC);
 #pragma unroll
-    for (int q = 0; q < 24 / EPC; ++q) {
+    for (int q = 0; q < 12 / EPC; ++q) {
         GT e[EPC];
         __builtin_memcpy(e, __builtin_assume_aligned(my + 1024 * q, 16), 16);
 #pragma unroll
@@ -588,38 +604,61 @@ __device__ inline void keep_read(const float* stage, GT v[8][3])
 // The stepper's source on the linear layout: GridField<GT, 0> with the kept
 // corner values.  Bound by the 128-byte lines the gathers move (about five per
 // cell; 6.8 TB/s of them): on 1e5 nuclei in a 250^3 FP32 grid of 50 kpc cells,
-// where 60% of the stages stay in their cell, 59 -> 32 ms.
+// where 60% of the stages stay in their cell, 59 -> 32 ms.  On 10 kpc cells, where
+// few do, 1e5 nuclei in a 256^3 FP64 grid took 48 to 55 ms without kept values and 42
+// with them (1000 to 1e6 nuclei, FP32 and FP64: never longer), so they are always
+// kept.
+//
+// Registers: with the cell's 24 values live once for the LDS writes and once for
+// the sums, the FP64 stepper on FP64 grids spilled 19 of them.  Now the loads all
+// stand before the writes, nothing else is moved in between, the values are read
+// back and summed by halves, and the cell is kept as one number: none.  Loading the
+// ends of a z-edge together took 1e6 nuclei on 10 kpc cells from 299 to 251 ms (FP64
+// grid) and from 260 to 200 ms (FP32), 1e5 on 50 kpc cells from 34.3 to 32.4 and from
+// 29.5 to 27.0 ms; half of the cell at a time needs still fewer registers, but two
+// trips to memory (5000 nuclei 14.8 -> 16.5 ms).
 template <class GT>
 struct LinearKeepField {
     GridView g;
     float* stage = nullptr;          // the wave's LDS area
-    int have[3] = {-1, -1, -1};      // the cell whose values this lane keeps
-    __device__ inline void corners(const Cell& c, GT v[8][3])
+    int64_t have = -1;               // the cell whose values this lane keeps
+    // the cell's corner values to the lane's slots, if another cell's are there
+    __device__ inline void fetch(const Cell& c)
     {
-        const int d = (c.i0[0] ^ have[0]) | (c.i0[1] ^ have[1]) | (c.i0[2] ^ have[2]);
-        if (d != 0) {
+        const int64_t cell = cell_index(g, c);
+        if (cell != have) {
+            have = cell;
             GT w[8][3];
-            gather_linear<GT>(g, c, w);
+            gather_linear<GT, true>(g, c, w);
+            __builtin_amdgcn_sched_barrier(0);
             keep_write(stage, w);
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-                have[a] = c.i0[a];
         }
-        keep_read(stage, v);
     }
     __device__ inline void fp64(const double p[3], double B[3], bool = true)
     {
         const Cell c = locate(g, p);
-        GT v[8][3];
-        corners(c, v);
-        interp_fp64(c.t, v, B);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(c);
+        __builtin_amdgcn_sched_barrier(0);
+        GT v[4][3];
+        keep_read(stage, 0, v);
+        interp_fp64_part<0, 4>(c.t, v, B);
+        __builtin_amdgcn_sched_barrier(0);
+        keep_read(stage, 1, v);
+        interp_fp64_part<4, 8>(c.t, v, B);
     }
     __device__ inline void fp32(const double p[3], float B[3], bool = true)
     {
         const Cell c = locate(g, p);
-        GT v[8][3];
-        corners(c, v);
-        interp_fp32(c.t, v, B);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(c);
+        __builtin_amdgcn_sched_barrier(0);
+        GT v[4][3];
+        keep_read(stage, 0, v);
+        interp_fp32_part<0, 4>(c.t, v, B);
+        __builtin_amdgcn_sched_barrier(0);
+        keep_read(stage, 1, v);
+        interp_fp32_part<4, 8>(c.t, v, B);
     }
 };
 

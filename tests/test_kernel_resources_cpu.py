@@ -58,3 +58,9 @@ def test_two_blocks_of_256_fit_with_the_largest_tables_on_fp32_records(kernels):
             assert 2 * need <= LDS, (mode, layout, traj, need)
             seen += 1
     assert seen == 8
+
+
+def test_no_spills(kernels):
+    """No vector register of a propagation kernel is spilled, and none uses scratch."""
+    for key, f in kernels.items():
+        assert int(f["vgpr_spill_count"]) == 0 and int(f["private_segment_fixed_size"]) == 0, key
