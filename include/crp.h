@@ -458,8 +458,9 @@ crp_status crp_last_timing(crp_ctx* ctx, double* kernel_ms, int64_t* launches);
  * (the cooperative corner-record gather of the propagation kernel) on this
  * context's corner records (built on first use, as for CRP_LAYOUT_CORNER),
  * `iters` random records per lane with the context's blocks per CU (block
- * 128).  records_per_s: gathered records per second, the practical ceiling of
- * the field evaluation.  CRP_ESTATE without a grid, CRP_EINVAL for an FP64 grid,
+ * 128).  records_per_s: gathered records per second, every one another record
+ * and waited for before the next is asked for (the stepper asks ahead and keeps
+ * the records of cells it stays in, so its gathers can be faster).  CRP_ESTATE without a grid, CRP_EINVAL for an FP64 grid,
  * a grid of more than 2^32 - 1 cells or iters < 1. */
 crp_status crp_gather_ceiling(crp_ctx* ctx, int32_t iters, double* records_per_s);
 

@@ -393,10 +393,14 @@ __device__ inline void gather_corner(const GridView& g, const Cell& c, float v[8
 // record follow each other with the same address registers.  Issuing a
 // record's pieces several instructions apart touches its line again while it
 // is under way: 18% slower on 1e6 candidates in a 512^3 FP32 grid (214 against
-// 180 ms).  The earlier mapping (chunk i of the wave's 384 or 768 chunks by lane
-// i mod 64) took a shuffle, an address and a mask test per chunk: 107 against
-// 95 ms on 1e5 candidates in a 256^3 FP64 grid, where few records of a wave
-// miss, and 181 against 180 ms in the 512^3 FP32 grid.  Within a piece the
+// 180 ms); so were the last 32 bytes of two groups moved by one load, without the
+// pad (133 -> 144 ms).  The earlier mapping (chunk i of the wave's 384 or 768 chunks
+// by lane i mod 64, no pad moved) takes a shuffle, an address and a mask test per
+// chunk.  Alone it is the faster for FP32 (crp_gather_ceiling on a 1024^3 grid:
+// 4.8e10 records per second against 4.4e10), but the stepper is the slower for it:
+// 107 against 95 ms on 1e5 candidates in a 256^3 FP64 grid, where few records of a
+// wave miss, 134.5 against 132.7 ms on 1e6 in the 512^3 FP32 grid, 196 against 190 ms
+// in a 256^3 FP32 grid with a patch.  Within a piece the
 // chunks are XOR-swizzled by the record number, so that the read-back of 16
 // consecutive lanes covers all LDS banks (it had 4-way conflicts for FP64).
 template <class GT>

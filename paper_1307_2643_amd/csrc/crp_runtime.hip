@@ -700,8 +700,9 @@ crp_status run_kernel(crp_ctx* ctx, int64_t max_cycles, DevCounters* dc, bool sp
     hipStream_t s = ctx->stream;
     if (neural) {
         const size_t nl = lds + NF_LDS_BYTES;
-        // the network, the tables and the per-lane state share the CU's LDS
-        if (nl + (size_t)256 * (7 * 8 + 7 * 4) + 256 > (size_t)160 * 1024)
+        // the network, the tables and the per-lane state share the CU's LDS (the
+        // limit counts 84 bytes a lane, which the state once took; it takes 60)
+        if (nl + (size_t)256 * 84 + 256 > (size_t)160 * 1024)
             return fail(ctx, CRP_EINVAL, "neural propagation: tables too large for LDS (n <= 200)");
         // the dynamic-LDS limit is a per-device function attribute: set it
         // once per context (each context is bound to one device)

@@ -97,3 +97,30 @@ def test_packed_patches(P, oracle_lib, precision, dtype, layout, refill):
                                                     (0, np.float64, 0)])
 def test_packed_blocks_of_256(P, oracle_lib, precision, dtype, layout):
     _compare(P, oracle_lib, "few", precision, dtype, layout, 16, block=256)
+
+
+@pytest.mark.parametrize("nodes", [2, 268, 269, 541, 653, 1024])
+@pytest.mark.parametrize("dtype,layout,block", [(np.float64, 0, 128), (np.float64, 1, 256),
+                                                (np.float32, 1, 256), (np.float32, 0, 128)])
+def test_table_sizes(P, oracle_lib, dtype, layout, block, nodes):
+    """Tables of 2 to 1024 nodes, which share a compute unit's LDS with the blocks' own areas:
+    fewer blocks fit beyond 268 (FP64 grid, block 128), 540 (FP64, 256) and 652 nodes (FP32
+    linear, 128)."""
+    O = oracle_lib
+    w = dataclasses.replace(I.W_SMALL, lmax_m=3 * I.MPC_M)
+    e = I.table_nodes(nodes)
+    full = I.tables_full()
+    tables = I.Tables(e, *(np.interp(e, full.e_nodes, v) for v in
+                           (full.t_pi, full.t_n, full.beta_p)))
+    grid = w.make_grid().astype(dtype)
+    inj = I.inject_mixed(700, 47, lmax_m=w.lmax_m, e1=1e19, e2=1e21)
+    say(f"tables of {nodes} nodes, {np.dtype(dtype).name}, layout {layout}, block {block}")
+    with make_ctx(P, w, grid, tables, 0) as ctx:
+        ctx.set_launch(block=block, layout=layout)
+        done, fin, neu, cnt = run_gpu(ctx, inj)
+    assert done
+    fo, no, co, _ = O.propagate(O.config_for(w), O.GridRef(grid, w.spacing_m),
+                                O.TablesRef(tables), inj)
+    assert compare_records(fin, fo, f"{nodes} nodes").all()
+    compare_neutral(neu, no, f"{nodes} nodes", fo)
+    compare_counts(cnt, co, f"{nodes} nodes")
