@@ -569,7 +569,7 @@ __device__ inline void interp_fp32(const double t[3], const GT v[8][3], float B[
 
 // The corner values of the cell each lane gathered last, kept in the wave's
 // staging area (16-byte chunk q of lane l in slot 64 q + l: no bank conflicts)
-// for the linear layouts, whose lanes gather on their own: a lane whose position
+// for the linear layout, whose lanes gather on their own: a lane whose position
 // stays in its cell reads them back instead of eight rows of the grid.
 template <class GT>
 constexpr int keep_float4 = 64 * (int)sizeof(GT) * 24 / 16;   // slots of a wave's area
@@ -605,13 +605,40 @@ __device__ inline void keep_read(const float* stage, int h, GT v[4][3])
     }
 }
 
-// The stepper's source on the linear layout: GridField<GT, 0> with the kept
-// corner values.  Bound by the 128-byte lines the gathers move (about five per
-// cell; 6.8 TB/s of them): on 1e5 nuclei in a 250^3 FP32 grid of 50 kpc cells,
-// where 60% of the stages stay in their cell, 59 -> 32 ms.  On 10 kpc cells, where
-// few do, 1e5 nuclei in a 256^3 FP64 grid took 48 to 55 ms without kept values and 42
-// with them (1000 to 1e6 nuclei, FP32 and FP64: never longer), so they are always
-// kept.
+// The stepper's source on the linear layout for small batches: every lane gathers its
+// own corner values.
+template <class GT>
+struct LinearField {
+    GridView g;
+    __device__ inline void fp64(const double p[3], double B[3], bool = true)
+    {
+        const Cell c = locate(g, p);
+        GT v[8][3];
+        gather_linear<GT, true>(g, c, v);
+        interp_fp64(c.t, v, B);
+    }
+    __device__ inline void fp32(const double p[3], float B[3], bool = true)
+    {
+        const Cell c = locate(g, p);
+        GT v[8][3];
+        gather_linear<GT, true>(g, c, v);
+        interp_fp32(c.t, v, B);
+    }
+};
+
+// From this many busy lanes of a wave on the corner values are kept.  Fewer lanes
+// wait for the latency of a gather, not for the lines it moves: the caches serve it,
+// and the way through LDS is longer.  Linear FP64 and FP32 grids, 50 kpc cells: 5000
+// candidates (5 lanes) 11.3 ms without and 13.5 with kept values, 30000 (30 lanes)
+// 15.7 and 17.4, 40000 18.2 and 18.2, 50000 21.0 and 19.1, 1e6 292 and 113; 10 kpc
+// cells: 5000 7.5 and 9.7, 40000 14.2 and 15.5 (FP32 11.5 and 12.3), 65000 19.9 and
+// 23.0 (16.0 and 15.9), 1e6 184 and 162 (151 and 128); 1000 protons in a 32^3 grid
+// 0.49 and 0.57.
+constexpr int KEEP_LANES = 41;
+
+// The source for the others: with kept corner values.  Bound by the 128-byte lines
+// the gathers move (about five per cell; 6.8 TB/s of them): on 1e5 nuclei in a 250^3
+// FP32 grid of 50 kpc cells, where 60% of the stages stay in their cell, 59 -> 32 ms.
 //
 // Registers: with the cell's 24 values live once for the LDS writes and once for
 // the sums, the FP64 stepper on FP64 grids spilled 19 of them.  Now the loads all

@@ -189,7 +189,8 @@ __device__ inline const T* opaque(const T* p)
     return p;
 }
 
-// Field source of a layout: 0 linear grid, 1 corner records (per lane),
+// Field source of a layout: 0 linear grid with kept corner values, 7 without,
+// 1 corner records (per lane),
 // 2 corner records gathered by the whole wave, 3 the neural field, 4 the
 // analytic galactic field, 5 the multi-resolution grid (linear base grid and
 // refinement patches), 6 the multi-resolution grid from corner records
@@ -201,6 +202,10 @@ struct FieldOf {
 template <class GT>
 struct FieldOf<GT, 0> {
     using T = LinearKeepField<GT>;
+};
+template <class GT>
+struct FieldOf<GT, 7> {
+    using T = LinearField<GT>;
 };
 template <class GT>
 struct FieldOf<GT, 3> {
@@ -336,7 +341,8 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
             F.stage = (float*)(stage_mem + wave * stage_float4<GT, LAYOUT>);
     } else {
         F.g = PP->grid;
-        F.stage = (float*)(stage_mem + wave * stage_float4<GT, LAYOUT>);
+        if constexpr (stage_float4<GT, LAYOUT> > 0)
+            F.stage = (float*)(stage_mem + wave * stage_float4<GT, LAYOUT>);
     }
     const StepParams sp = PP->sp;
     const int lane = lane_id();
@@ -1003,14 +1009,14 @@ __global__ void __launch_bounds__(BS, (min_waves<MODE, LAYOUT>))
 }
 
 // Explicit instantiations: FP64 / mixed stage arithmetic x grid element type x
-// grid layout (per-lane corner records and multi-resolution corner records
-// exist for FP32 grids only).
+// grid layout (multi-resolution corner records exist for FP32 grids only).
 #define CRP_INST(MODE, GT, LAYOUT)                                                          \
     template __global__ void k_propagate<MODE, GT, LAYOUT, 128, false>(const PropParams*); \
     template __global__ void k_propagate<MODE, GT, LAYOUT, 256, false>(const PropParams*); \
     template __global__ void k_propagate<MODE, GT, LAYOUT, 128, true>(const PropParams*);  \
     template __global__ void k_propagate<MODE, GT, LAYOUT, 256, true>(const PropParams*);
 CRP_INST(MODE_FP64, double, 0)
+CRP_INST(MODE_FP64, double, 7)
 CRP_INST(MODE_FP64, double, 2)
 CRP_INST(MODE_FP64, double, 4)
 CRP_INST(MODE_FP64, double, 5)
@@ -1021,10 +1027,13 @@ CRP_INST(MODE_MIX, float, 6)
 CRP_INST(MODE_FP64, float, 6)
 CRP_INST(MODE_MIX, double, 4)
 CRP_INST(MODE_FP64, float, 0)
+CRP_INST(MODE_FP64, float, 7)
 CRP_INST(MODE_FP64, float, 2)
 CRP_INST(MODE_MIX, double, 0)
+CRP_INST(MODE_MIX, double, 7)
 CRP_INST(MODE_MIX, double, 2)
 CRP_INST(MODE_MIX, float, 0)
+CRP_INST(MODE_MIX, float, 7)
 CRP_INST(MODE_MIX, float, 2)
 #undef CRP_INST
 // neural field (precision form, one block of 256 per CU: the network fills LDS)

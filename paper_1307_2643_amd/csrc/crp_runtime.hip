@@ -307,6 +307,30 @@ void launch_propagate(int nb, int bs, size_t lds, hipStream_t s, const PropParam
         k_propagate<MODE, GT, LAYOUT, 256, false><<<nb, 256, lds, s>>>(dp);
 }
 
+// The two steppers of the linear layout: 0 with kept corner values, 7 without.
+template <int LAYOUT>
+int linear_blocks(bool mix, bool f32, int bs, size_t lds)
+{
+    return mix ? (f32 ? resident_blocks<MODE_MIX, float, LAYOUT>(bs, lds)
+                      : resident_blocks<MODE_MIX, double, LAYOUT>(bs, lds))
+               : (f32 ? resident_blocks<MODE_FP64, float, LAYOUT>(bs, lds)
+                      : resident_blocks<MODE_FP64, double, LAYOUT>(bs, lds));
+}
+
+template <int LAYOUT>
+void launch_linear(bool mix, bool f32, int nb, int bs, size_t lds, hipStream_t s,
+                   const PropParams* dp, bool traj)
+{
+    if (mix && f32)
+        launch_propagate<MODE_MIX, float, LAYOUT>(nb, bs, lds, s, dp, traj);
+    else if (mix)
+        launch_propagate<MODE_MIX, double, LAYOUT>(nb, bs, lds, s, dp, traj);
+    else if (f32)
+        launch_propagate<MODE_FP64, float, LAYOUT>(nb, bs, lds, s, dp, traj);
+    else
+        launch_propagate<MODE_FP64, double, LAYOUT>(nb, bs, lds, s, dp, traj);
+}
+
 // [start, start+k) of a planar [3][cap] array as [k][3] (a thread per row, grid
 // stride: coalesced reads of each plane, 24-byte rows written side by side).
 __global__ void k_interleave3(const double* __restrict__ planar, int64_t cap, int64_t start,
@@ -643,6 +667,7 @@ crp_status run_kernel(crp_ctx* ctx, int64_t max_cycles, DevCounters* dc, bool sp
     const size_t lds = lds_bytes(ctx->tab_n, bs);
     const bool mix = c.precision == CRP_MIX;
     const bool f32 = ctx->grid_dtype == CRP_F32;
+    const bool linear = !neural && !analytic && !nested && layout == CRP_LAYOUT_LINEAR;
     int bpc = ctx->launch.blocks_per_cu;
     if (bpc == 0) {   // as many blocks as fit on a compute unit
         if (nested && f32 && layout == CRP_LAYOUT_CORNER)
@@ -657,22 +682,16 @@ crp_status run_kernel(crp_ctx* ctx, int64_t max_cycles, DevCounters* dc, bool sp
         else if (analytic)
             bpc = mix ? resident_blocks<MODE_MIX, double, 4>(bs, lds)
                       : resident_blocks<MODE_FP64, double, 4>(bs, lds);
-        else if (!mix && !f32 && layout == CRP_LAYOUT_CORNER)
-            bpc = resident_blocks<MODE_FP64, double, 2>(bs, lds);
+        else if (linear || neural)
+            bpc = linear_blocks<0>(mix, f32, bs, lds);
         else if (!mix && !f32)
-            bpc = resident_blocks<MODE_FP64, double, 0>(bs, lds);
-        else if (!mix && layout == CRP_LAYOUT_CORNER)
-            bpc = resident_blocks<MODE_FP64, float, 2>(bs, lds);
+            bpc = resident_blocks<MODE_FP64, double, 2>(bs, lds);
         else if (!mix)
-            bpc = resident_blocks<MODE_FP64, float, 0>(bs, lds);
-        else if (!f32 && layout == CRP_LAYOUT_CORNER)
-            bpc = resident_blocks<MODE_MIX, double, 2>(bs, lds);
+            bpc = resident_blocks<MODE_FP64, float, 2>(bs, lds);
         else if (!f32)
-            bpc = resident_blocks<MODE_MIX, double, 0>(bs, lds);
-        else if (layout == CRP_LAYOUT_CORNER)
-            bpc = resident_blocks<MODE_MIX, float, 2>(bs, lds);
+            bpc = resident_blocks<MODE_MIX, double, 2>(bs, lds);
         else
-            bpc = resident_blocks<MODE_MIX, float, 0>(bs, lds);
+            bpc = resident_blocks<MODE_MIX, float, 2>(bs, lds);
     }
     int nb = ctx->num_cus * bpc;
     // Fewer candidates than lanes of one wave per SIMD (or of the launch's waves,
@@ -689,6 +708,10 @@ crp_status run_kernel(crp_ctx* ctx, int64_t max_cycles, DevCounters* dc, bool sp
     P.lane_cap = 64;
     if (spread && !neural && ctx->pending < 64 * waves)
         P.lane_cap = (int)((ctx->pending + waves - 1) / waves);
+    // few lanes busy: the linear layout's stepper without kept corner values
+    const bool plain = linear && P.lane_cap < KEEP_LANES;
+    if (plain && ctx->launch.blocks_per_cu == 0)
+        nb = ctx->num_cus * linear_blocks<7>(mix, f32, bs, lds);
     P.no_append = ctx->no_channels ? 1 : 0;
     if (spread && ctx->no_channels) {
         const int64_t per_block = (int64_t)P.lane_cap * waves_per_block;
@@ -736,22 +759,18 @@ crp_status run_kernel(crp_ctx* ctx, int64_t max_cycles, DevCounters* dc, bool sp
         launch_propagate<MODE_MIX, double, 4>(nb, bs, lds, s, dp, traj);
     else if (analytic)
         launch_propagate<MODE_FP64, double, 4>(nb, bs, lds, s, dp, traj);
-    else if (!mix && !f32 && layout == CRP_LAYOUT_CORNER)
-        launch_propagate<MODE_FP64, double, 2>(nb, bs, lds, s, dp, traj);
+    else if (plain)
+        launch_linear<7>(mix, f32, nb, bs, lds, s, dp, traj);
+    else if (linear)
+        launch_linear<0>(mix, f32, nb, bs, lds, s, dp, traj);
     else if (!mix && !f32)
-        launch_propagate<MODE_FP64, double, 0>(nb, bs, lds, s, dp, traj);
-    else if (!mix && layout == CRP_LAYOUT_CORNER)
-        launch_propagate<MODE_FP64, float, 2>(nb, bs, lds, s, dp, traj);
+        launch_propagate<MODE_FP64, double, 2>(nb, bs, lds, s, dp, traj);
     else if (!mix)
-        launch_propagate<MODE_FP64, float, 0>(nb, bs, lds, s, dp, traj);
-    else if (!f32 && layout == CRP_LAYOUT_CORNER)
-        launch_propagate<MODE_MIX, double, 2>(nb, bs, lds, s, dp, traj);
+        launch_propagate<MODE_FP64, float, 2>(nb, bs, lds, s, dp, traj);
     else if (!f32)
-        launch_propagate<MODE_MIX, double, 0>(nb, bs, lds, s, dp, traj);
-    else if (layout == CRP_LAYOUT_CORNER)
-        launch_propagate<MODE_MIX, float, 2>(nb, bs, lds, s, dp, traj);
+        launch_propagate<MODE_MIX, double, 2>(nb, bs, lds, s, dp, traj);
     else
-        launch_propagate<MODE_MIX, float, 0>(nb, bs, lds, s, dp, traj);
+        launch_propagate<MODE_MIX, float, 2>(nb, bs, lds, s, dp, traj);
     }
     HIPCHK(ctx, hipGetLastError());
     HIPCHK(ctx, hipEventRecord(ctx->ev1, ctx->stream));

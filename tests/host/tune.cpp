@@ -3,16 +3,9 @@
 //   tune trials        every trial is launched as a large batch is
 //   tune keep PCT      with three blocks per unit PCT percent faster than the filled
 //                      unit on the calibration batch: prints the shape that is kept
-#include "fake_hip.hpp"
+#include "small_context.hpp"
 
-#include "crp.h"
 #include "crp_internal.hpp"
-
-static int check(bool ok, const std::string& what)
-{
-    std::printf("%s: %s\n", ok ? "ok" : "FAILED", what.c_str());
-    return ok ? 0 : 1;
-}
 
 struct Launch {
     int blocks, threads, lane_cap, refill, no_append;
@@ -37,42 +30,12 @@ int main(int argc, char** argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     fake::on_launch = kernel;
-    crp_config c;
-    std::memset(&c, 0, sizeof c);
-    c.precision = CRP_FP64;
-    c.field_mode = CRP_FIELD_GRID;
-    c.renormalize = 1;
-    c.tol = 1e-4;
-    c.hmin = 1e20;
-    c.hmax = 1e22;
-    c.eps_loss = 0.1;
-    c.seed = 1;
-    c.queue_capacity = 4096;
-    c.neutral_capacity = 16;
-    crp_ctx* ctx = nullptr;
-    int bad = check(crp_create(&c, nullptr, &ctx) == CRP_OK, "create");
-    if (bad)
-        return bad;
-    std::vector<double> grid(4 * 4 * 4 * 3, 1e-13);
-    const double origin[3] = {0, 0, 0};
-    bad += check(crp_set_field_grid(ctx, grid.data(), CRP_F64, 0, 4, 4, 4, 1e21, origin) == CRP_OK,
-                 "grid");
-    const double e[2] = {1e17, 1e21}, zero[2] = {0, 0}, open[2] = {1e-25, 1e-25};
-    const bool channels = what == "keep";
-    bad += check(crp_set_tables(ctx, 2, e, channels ? open : zero, channels ? open : zero, zero) ==
-                     CRP_OK,
-                 "tables");
     const int n = 300;
-    std::vector<uint32_t> id(n);
-    std::vector<int32_t> A(n, 1), Z(n, 1);
-    std::vector<double> E(n, 1e19), pos(3 * n, 0.0), dir(3 * n, 0.0), lmax(n, 1e22);
-    for (int i = 0; i < n; ++i) {
-        id[i] = (uint32_t)i;
-        dir[3 * i] = 1.0;
-    }
-    bad += check(crp_inject(ctx, n, id.data(), A.data(), Z.data(), E.data(), pos.data(),
-                            dir.data(), lmax.data(), 0) == CRP_OK,
-                 "inject");
+    crp_ctx* ctx = make_context(4096);
+    if (!ctx)
+        return 1;
+    int bad = check(set_tables(ctx, what == "keep") == CRP_OK, "tables");
+    bad += check(inject(ctx, n) == CRP_OK, "inject");
     if (what == "keep")
         three_faster = std::atof(argv[2]);
     crp_launch best;

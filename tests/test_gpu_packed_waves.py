@@ -35,14 +35,15 @@ def _batch(n, lmax, box):
     return inj
 
 
-def _compare(P, O, shape, precision, dtype, layout, refill, patches=(), block=128):
+def _compare(P, O, shape, precision, dtype, layout, refill, patches=(), block=128, n=None):
     dims, step = SHAPES[shape]
     w = dataclasses.replace(I.W_SMALL, tables="full", hmin_m=0.02 * step * CELL,
                             hmax_m=step * CELL, lmax_m=max(25 * step * CELL, I.MPC_M))
     rng = np.random.default_rng(5)
     grid = (rng.standard_normal(dims + (3,)) * 1e-13).astype(dtype)
     tables = w.make_tables()
-    n = N * block // 128
+    full = n is None
+    n = N * block // 128 if full else n
     inj = _batch(n, w.lmax_m, np.array(dims) * CELL)
     say(f"packed {shape} precision {precision} {np.dtype(dtype).name} layout {layout} "
         f"refill {refill} patches {len(patches)}")
@@ -56,8 +57,8 @@ def _compare(P, O, shape, precision, dtype, layout, refill, patches=(), block=12
                                 O.GridRef(grid, w.spacing_m, patches=list(patches)),
                                 O.TablesRef(tables), inj, fin_cap=4 * n, neu_cap=4 * n)
     # (a spread batch has a sixty-fourth of the lanes busy)
-    assert cnt["attempts"] > 0.2 * cnt["lane_slots"]
-    assert co["charged_sec"] > 1000 and co["neutral_sec"] > 100
+    assert not full or cnt["attempts"] > 0.2 * cnt["lane_slots"]
+    assert co["charged_sec"] > 500 and co["neutral_sec"] > 100
     assert compare_records(fin, fo, shape).all()
     compare_neutral(neu, no, shape, fo)
     compare_counts(cnt, co, shape)
@@ -78,6 +79,15 @@ def test_packed_corner_records(P, oracle_lib, precision, dtype, shape, refill):
                          ids=["fp64-f64", "mix-f64", "fp64-f32", "mix-f32"])
 def test_packed_linear(P, oracle_lib, precision, dtype, shape, refill):
     _compare(P, oracle_lib, shape, precision, dtype, P.LAYOUT_LINEAR, refill)
+
+
+@pytest.mark.parametrize("lanes,more", [(40, 0), (40, 1), (64, -1)])
+@pytest.mark.parametrize("precision,dtype", [(0, np.float64), (1, np.float64), (0, np.float32),
+                                             (1, np.float32)],
+                         ids=["fp64-f64", "mix-f64", "fp64-f32", "mix-f32"])
+def test_linear_around_the_change_of_stepper(P, oracle_lib, precision, dtype, lanes, more):
+    """40 lanes of each of the 512 waves (no values kept), 41 (kept), and all but one."""
+    _compare(P, oracle_lib, "few", precision, dtype, P.LAYOUT_LINEAR, 4, n=512 * lanes + more)
 
 
 @pytest.mark.parametrize("refill", [1, 64])

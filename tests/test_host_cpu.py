@@ -47,3 +47,11 @@ def test_tuner_takes_fewer_waves_only_beyond_the_noise(driver, percent, kept):
     """Three blocks per compute unit instead of the filled unit: kept when they are faster by
     more than the calibration's noise (3 percent), not within it."""
     assert f"kept {kept}\n" in run(driver("tune"), "keep", str(percent))
+
+
+@pytest.mark.parametrize("n,layout,lanes", [(1, 7, 1), (1024, 7, 1), (40960, 7, 40), (40961, 0, 41),
+                                            (65536, 0, 64), (200000, 0, 64)])
+def test_linear_layout_keeps_corner_values_of_large_batches_only(driver, n, layout, lanes):
+    """Kept corner values (0) from 41 lanes of a wave on, plain gathers (7) below (256 compute
+    units, four waves each)."""
+    assert f"layout {layout} lanes {lanes} " in run(driver("linear_rule"), str(n))
