@@ -434,19 +434,22 @@ crp_status crp_get_launch(crp_ctx* ctx, crp_launch* launch);
  * the linear and the corner layout (the corner layout only where its records
  * can be built: they fit in device memory, the grid has fewer than 2^32
  * cells, and it is not an FP64 grid with refinement patches); then, around
- * the fastest of those, refill
- * 1 and 64 and 2 blocks per compute unit.  The trials run on a copy of the
- * pending queue (restored after each trial, so the
- * pending work is unchanged) run for max_cycles cycles (<= 0: to completion),
- * launched with full waves and all blocks as a large batch is, even if the
- * pending work is few; keeps the fastest in the context (one with fewer blocks
- * per compute unit than fit only if it is faster by more than 3%, which is the
- * trials' noise) and appends it to cache_path (NULL: no file) under a key of (device name, grid shape, dtype, precision, field
- * mode).  If cache_path already holds an entry for this key, its latest shape
- * is taken without trials.  best_rate: accepted steps per second of the chosen
- * shape (from the cache when taken from it).  Needs pending work unless the
- * cache answers.  Errors: CRP_ESTATE (no grid, tables or pending work; not the
- * grid field mode), CRP_EDEVICE. */
+ * the fastest of those, refill 1 and 64 and 2 blocks per compute unit.  A
+ * batch small enough to be spread (see crp_set_launch: fewer pending candidates
+ * than 256 per compute unit) is the same launch for every refill and number of
+ * blocks: block and layout alone are tried.  The trials run on a copy of the
+ * pending queue (restored after each trial, so the pending work is unchanged)
+ * run for max_cycles cycles (<= 0: to completion).  The fastest shape is kept in
+ * the context (one with fewer blocks per compute unit than fit or another refill
+ * than 4 only if it is faster by more than 3%, which is the trials' noise) and
+ * appended to cache_path (NULL: no file) under a key of (device name, grid
+ * shape, dtype, precision, field mode, whether the batch is small).  If
+ * cache_path already holds an entry for this key, its latest shape is taken
+ * without trials; without pending work that of large batches, or else of small
+ * ones.  best_rate: accepted steps per second of the chosen shape (from the cache
+ * when taken from it).  Needs pending work unless the cache answers.  Errors:
+ * CRP_ESTATE (no grid, tables or pending work; not the grid field mode),
+ * CRP_EDEVICE. */
 crp_status crp_tune(crp_ctx* ctx, int64_t max_cycles, const char* cache_path,
                     crp_launch* best, double* best_rate);
 

@@ -588,10 +588,8 @@ void free_corner(crp_ctx* ctx)
 }
 
 // Launches one propagation run over the pending queue (no host bookkeeping
-// of totals).  On return the device counter block is in *dc.  spread: a small batch
-// is spread over the waves (below); the autotuner's trials are not, so that the
-// shape it times is the one that a large batch gets.
-crp_status run_kernel(crp_ctx* ctx, int64_t max_cycles, DevCounters* dc, bool spread = true)
+// of totals).  On return the device counter block is in *dc.
+crp_status run_kernel(crp_ctx* ctx, int64_t max_cycles, DevCounters* dc)
 {
     DevCounters init;
     std::memset(&init, 0, sizeof init);
@@ -706,14 +704,14 @@ crp_status run_kernel(crp_ctx* ctx, int64_t max_cycles, DevCounters* dc, bool sp
     const int64_t waves = std::min<int64_t>((int64_t)ctx->num_cus * 4,
                                             (int64_t)nb * waves_per_block);
     P.lane_cap = 64;
-    if (spread && !neural && ctx->pending < 64 * waves)
+    if (!neural && ctx->pending < 64 * waves)
         P.lane_cap = (int)((ctx->pending + waves - 1) / waves);
     // few lanes busy: the linear layout's stepper without kept corner values
     const bool plain = linear && P.lane_cap < KEEP_LANES;
     if (plain && ctx->launch.blocks_per_cu == 0)
         nb = ctx->num_cus * linear_blocks<7>(mix, f32, bs, lds);
     P.no_append = ctx->no_channels ? 1 : 0;
-    if (spread && ctx->no_channels) {
+    if (ctx->no_channels) {
         const int64_t per_block = (int64_t)P.lane_cap * waves_per_block;
         nb = (int)std::min<int64_t>(nb, (ctx->pending + per_block - 1) / per_block);
     }
@@ -939,14 +937,16 @@ crp_status grow_queue(crp_ctx* ctx, int64_t cap)
 // -------------------------------------------------------------------------
 // Autotuner cache: one line per tuning, "KEY : block=B blocks_per_cu=C
 // refill=R layout=L steps_per_s=S", KEY naming the device, the grid shape and
-// element type, the precision and the field mode.
+// element type, the precision and the field mode, and whether the batch was small
+// enough to be spread over the waves (its launch is another one).
 // -------------------------------------------------------------------------
-static std::string tune_key(const crp_ctx* ctx)
+static std::string tune_key(const crp_ctx* ctx, bool small)
 {
     char buf[256];
-    snprintf(buf, sizeof buf, "%s grid=%lldx%lldx%lld dtype=%d precision=%d field=%d",
+    snprintf(buf, sizeof buf, "%s grid=%lldx%lldx%lld dtype=%d precision=%d field=%d%s",
              ctx->device_name.c_str(), (long long)ctx->gn[0], (long long)ctx->gn[1],
-             (long long)ctx->gn[2], ctx->grid_dtype, ctx->cfg.precision, ctx->cfg.field_mode);
+             (long long)ctx->gn[2], ctx->grid_dtype, ctx->cfg.precision, ctx->cfg.field_mode,
+             small ? " batch=small" : "");
     return buf;
 }
 
@@ -2188,13 +2188,18 @@ crp_status crp_tune(crp_ctx* ctx, int64_t max_cycles, const char* cache_path, cr
         return fail(ctx, CRP_ESTATE, "tune: set grid and tables first");
     if (ctx->cfg.field_mode != CRP_FIELD_GRID)
         return fail(ctx, CRP_ESTATE, "tune: grid field mode only");
-    // a shape tuned earlier for this device, grid, element type, precision
-    // and field mode: taken from the cache without trials (the latest entry)
-    const std::string key = tune_key(ctx);
+    // fewer candidates than four waves per compute unit have lanes: run_kernel
+    // spreads them, whatever the shape
+    const bool small = ctx->pending > 0 && ctx->pending < (int64_t)64 * 4 * ctx->num_cus;
+    const std::string key = tune_key(ctx, small);
+    // a shape tuned earlier for this key: taken from the cache without trials (the
+    // latest entry; without pending work that of large batches, if there is one)
     if (cache_path) {
         crp_launch cached;
         double rate = 0.0;
-        if (tune_cache_lookup(cache_path, key, &cached, &rate)) {
+        if (tune_cache_lookup(cache_path, key, &cached, &rate) ||
+            (ctx->pending == 0 &&
+             tune_cache_lookup(cache_path, tune_key(ctx, true), &cached, &rate))) {
             ctx->launch = cached;
             if (best)
                 *best = cached;
@@ -2226,13 +2231,14 @@ crp_status crp_tune(crp_ctx* ctx, int64_t max_cycles, const char* cache_path, cr
     crp_launch bestl = orig;
     double bestr = -1.0, bests = -1.0;
     crp_status st = CRP_OK;
-    // Fewer blocks per compute unit than fit have to win by more than the trials'
-    // noise: a short calibration run is decided by its end, where few waves work
-    // whatever the shape, and hides what the waves in flight are worth in a long
-    // one.  Distances 1-1000 Mpc, 1024^3 FP32 grid, block 128, refill 4: 1e6
-    // candidates 674-679 ms with the filled unit and 684-685 ms with three blocks
-    // (two trials of a shape differ by up to 1.5%), 1e7 candidates 5301 against 5833.
-    constexpr double FEWER_BLOCKS_GAIN = 1.03;
+    // Fewer blocks per compute unit than fit, and another refill threshold than 4,
+    // have to win by more than the trials' noise: a short calibration run is decided
+    // by its end, where few waves work whatever the shape, and hides what the waves
+    // in flight and their full lanes are worth in a long one.  Distances 1-1000 Mpc,
+    // 1024^3 FP32 grid, block 128: 1e6 candidates 674-679 ms with the filled unit and
+    // refill 4, 684-685 ms with three blocks, 682-687 ms with refill 16 (two trials of
+    // a shape differ by up to 1.5%); 1e7 candidates 5301 against 5833 and 5397 ms.
+    constexpr double NOISE = 1.03;
     // every shape is timed twice on the same work and keeps its better rate
     // (a single short trial is too noisy to separate shapes a few % apart)
     auto trial = [&](const crp_launch& l) {
@@ -2253,12 +2259,13 @@ crp_status crp_tune(crp_ctx* ctx, int64_t max_cycles, const char* cache_path, cr
             ctx->traj_unread = traj0;
             ctx->launch = l;
             DevCounters dc;
-            st = run_kernel(ctx, max_cycles, &dc, false);
+            st = run_kernel(ctx, max_cycles, &dc);
             if (st != CRP_OK)
                 break;
             const double rate =
                 ctx->last_ms > 0 ? (double)dc.steps / (ctx->last_ms * 1e-3) : 0.0;
-            const double score = l.blocks_per_cu == 0 ? rate : rate / FEWER_BLOCKS_GAIN;
+            const double score =
+                l.blocks_per_cu == 0 && l.refill == 4 ? rate : rate / NOISE;
             if (score > bests) {
                 bests = score;
                 bestr = rate;
@@ -2280,15 +2287,17 @@ crp_status crp_tune(crp_ctx* ctx, int64_t max_cycles, const char* cache_path, cr
         else if (cs != CRP_OK)
             st = cs;
     }
+    // (a spread batch runs a few lanes of each wave: refill and blocks per unit make
+    // no difference to it and stay 4 and the filled unit)
     for (int layout = 0; layout < (corner_ok ? 2 : 1) && st == CRP_OK; ++layout)
         for (const crp_launch& l : {crp_launch{128, 0, 4, 0}, crp_launch{128, 0, 16, 0},
                                     crp_launch{128, 3, 4, 0}, crp_launch{256, 0, 4, 0},
                                     crp_launch{256, 0, 16, 0}})
-            if (st == CRP_OK)
+            if (st == CRP_OK && !(small && (l.blocks_per_cu != 0 || l.refill != 4)))
                 trial(crp_launch{l.block, l.blocks_per_cu, l.refill, layout});
     // stage 2, around the best: the extreme refill thresholds (claim as soon as
     // one lane idles, or only when the whole wave has) and two blocks per CU
-    if (st == CRP_OK) {
+    if (st == CRP_OK && !small) {
         const crp_launch c = bestl;
         for (const crp_launch& l : {crp_launch{c.block, c.blocks_per_cu, 1, c.layout},
                                     crp_launch{c.block, c.blocks_per_cu, 64, c.layout},

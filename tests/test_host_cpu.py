@@ -38,15 +38,32 @@ def test_failed_injection_waits_for_its_upload(driver, kernel):
     run(driver("inject_failure"), kernel)
 
 
-def test_tuner_trials_are_launched_as_large_batches(driver):
-    run(driver("tune"), "trials")
+def test_tuner_tries_what_makes_a_difference_to_the_batch(driver):
+    """A batch that is spread over the waves is one launch for all refill thresholds and numbers
+    of blocks, which are not tried then; a large one is tried in full waves."""
+    def trials(n):
+        out = run(driver("tune"), "shapes", str(n)).splitlines()
+        return [t.split()[1:] for t in out if t.startswith("trial")], out[-1]
+    few, kept = trials(3000)
+    assert len(few) == 8 and len(set(map(tuple, few))) == 4      # two of each
+    assert {t[5] for t in few} == {"3"} and {t[7] for t in few} == {"4"}
+    assert kept.endswith("blocks 0 refill 4")
+    many, _ = trials(70000)
+    assert {t[5] for t in many} == {"64"} and {t[7] for t in many} == {"1", "4", "16", "64"}
 
 
-@pytest.mark.parametrize("percent,kept", [(1.5, "128 0"), (-1.5, "128 0"), (5.0, "128 3")])
-def test_tuner_takes_fewer_waves_only_beyond_the_noise(driver, percent, kept):
-    """Three blocks per compute unit instead of the filled unit: kept when they are faster by
-    more than the calibration's noise (3 percent), not within it."""
-    assert f"kept {kept}\n" in run(driver("tune"), "keep", str(percent))
+@pytest.mark.parametrize("three,sixteen,kept", [(1.5, 0, "128 blocks 0 refill 4"),
+                                                (0, 1.5, "128 blocks 0 refill 4"),
+                                                (5, 0, "128 blocks 3 refill 4"),
+                                                (0, 5, "128 blocks 0 refill 16")])
+def test_tuner_leaves_the_default_only_beyond_the_noise(driver, three, sixteen, kept):
+    """Three blocks per compute unit instead of the filled unit, or another refill threshold: kept
+    when faster by more than the calibration's noise (3 percent), not within it."""
+    assert f"kept block {kept}\n" in run(driver("tune"), "keep", str(three), str(sixteen))
+
+
+def test_tuner_cache_tells_small_batches_from_large(driver, tmp_path):
+    run(driver("tune"), "cache", str(tmp_path / "tune.txt"))
 
 
 @pytest.mark.parametrize("n,layout,lanes", [(1, 7, 1), (1024, 7, 1), (40960, 7, 40), (40961, 0, 41),
