@@ -695,7 +695,7 @@ crp_status run_kernel(crp_ctx* ctx, int64_t max_cycles, DevCounters* dc)
     // Fewer candidates than lanes of one wave per SIMD (or of the launch's waves,
     // if those are fewer): spread over these waves instead of packed 64 to a
     // wave, since an attempt's time grows with the lanes that gather (1000
-    // protons on the 32^3 FP64 grid: 1.13 -> 0.58 ms).  Beyond that they are
+    // protons on the 32^3 FP64 grid: 1.13 -> 0.50 ms).  Beyond that they are
     // packed, as a second wave on a SIMD slows the first.  Where no channel is
     // open nothing is appended during the run, and the blocks without a candidate
     // are not launched.  The network stepper's waves cost the same however many
